@@ -307,79 +307,137 @@ __global__ __launch_bounds__(NB_T) void k_nb_kick_drift_stream(const Side s, uin
 // Energy in FP64 (deterministic fixed-order reductions)
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(NB_T) void k_nb_decode64(const Side s, uint32_t n, double* __restrict__ d,
-                                                     const NbCount cnt) {
-  const uint32_t i = blockIdx.x * NB_T + threadIdx.x;
-  if (cnt.fac || cnt.heat[0])
-    for (uint32_t f = 0; f < 7; ++f) nb_count(cnt, s, f, 0, i, i < n);
-  if (i >= n) return;
-  for (uint32_t f = 0; f < 7; ++f) d[(size_t)f * n + i] = (double)nb_load(s, i, f);
-}
-
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  red[threadIdx.x] = v;
+// Sum over a workgroup of W waves in a fixed order; every thread takes part,
+// the result is valid on thread 0.
+template <uint32_t W>
+__device__ __forceinline__ double block_sum(double v) {
+  __shared__ double red[W];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if (lane_id() == 0) red[wave_id()] = v;
   __syncthreads();
-  for (uint32_t w = NB_T / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  const double r = red[0];
+  double r = 0.0;
+#pragma unroll
+  for (uint32_t w = 0; w < W; ++w) r += red[w];
   __syncthreads();
   return r;
 }
 
-// block (bi, bj), bj >= bi: sum over i in block bi, j in block bj, j > i of
-// m_i m_j / sqrt(|x_i - x_j|^2 + eps2); blocks with bj < bi write 0.
-__global__ __launch_bounds__(NB_T) void k_nb_potential(const double* __restrict__ d, uint32_t n, double eps2,
-                                                      double* __restrict__ partial) {
-  __shared__ double red[NB_T];
-  __shared__ double4 tj[NB_T];
-  const uint32_t bi = blockIdx.x, bj = blockIdx.y;
-  double acc = 0.0;
-  if (bj >= bi) {
-    const uint32_t j = bj * NB_T + threadIdx.x;
-    tj[threadIdx.x] = j < n ? double4{d[j], d[n + j], d[2u * n + j], d[6u * n + j]} : double4{0, 0, 0, 0};
-    __syncthreads();
-    const uint32_t i = bi * NB_T + threadIdx.x;
-    if (i < n) {
-      const double xi = d[i], yi = d[n + i], zi = d[2u * n + i], mi = d[6u * n + i];
-      for (uint32_t k = 0; k < NB_T; ++k) {
-        const uint32_t jj = bj * NB_T + k;
-        if (jj <= i || jj >= n) continue;
-        const double4 q = tj[k];
-        const double dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
-        acc += q.w / sqrt(dx * dx + dy * dy + dz * dz + eps2);
-      }
-      acc *= mi;
-    }
-  }
-  const double t = block_sum(acc, red);
-  if (threadIdx.x == 0) partial[(size_t)bi * gridDim.y + bj] = t;
-}
-
-__global__ __launch_bounds__(NB_T) void k_nb_kinetic(const double* __restrict__ d, uint32_t n,
-                                                    double* __restrict__ partial) {
-  __shared__ double red[NB_T];
+// Decodes the particles into {x, y, z, m} rows of doubles (`pm`) and sums each
+// block's kinetic energy.
+__global__ __launch_bounds__(NB_T) void k_nb_decode64(const Side s, uint32_t n, double4* __restrict__ pm,
+                                                     double* __restrict__ kin, const NbCount cnt) {
   const uint32_t i = blockIdx.x * NB_T + threadIdx.x;
+  if (cnt.fac || cnt.heat[0])
+    for (uint32_t f = 0; f < 7; ++f) nb_count(cnt, s, f, 0, i, i < n);
   double k = 0.0;
   if (i < n) {
-    const double vx = d[3u * n + i], vy = d[4u * n + i], vz = d[5u * n + i];
-    k = 0.5 * d[6u * n + i] * (vx * vx + vy * vy + vz * vz);
+    const double m = (double)nb_load(s, i, 6);
+    const double vx = (double)nb_load(s, i, 3), vy = (double)nb_load(s, i, 4), vz = (double)nb_load(s, i, 5);
+    pm[i] = double4{(double)nb_load(s, i, 0), (double)nb_load(s, i, 1), (double)nb_load(s, i, 2), m};
+    k = 0.5 * m * (vx * vx + vy * vy + vz * vz);
   }
-  const double t = block_sum(k, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = t;
+  const double t = block_sum<NB_T / 64>(k);
+  if (threadIdx.x == 0) kin[blockIdx.x] = t;
 }
 
-// result = sum(kin[0..nk)) - sum(pot[0..np)), summed by one workgroup in fixed order
-__global__ __launch_bounds__(NB_T) void k_nb_final(const double* __restrict__ kin, uint32_t nk,
-                                                  const double* __restrict__ pot, uint32_t np,
-                                                  double* __restrict__ out) {
-  __shared__ double red[NB_T];
-  double k = 0.0, p = 0.0;
-  for (uint32_t q = threadIdx.x; q < nk; q += NB_T) k += kin[q];
-  for (uint32_t q = threadIdx.x; q < np; q += NB_T) p += pot[q];
-  const double ks = block_sum(k, red);
-  const double ps = block_sum(p, red);
+// 1 / sqrt(x) of a normal x > 0 to the last place: v_rsq_f64 (about 23 bits)
+// and one third-order step, y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2,
+// whose error is 5 / 16 e^3.
+__device__ __forceinline__ double rsqrt64(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+// sum over j in [j0, j1) of m_j (|x_i - x_j|^2 + eps2)^(-1/2), over j > i only
+// with DIAG.  The j rows are uniform: they come through scalar loads and the
+// arithmetic reads them as scalar operands.  FAST: every distance is finite
+// and eps2 > 0.
+template <bool DIAG, bool FAST>
+__device__ __forceinline__ double pair_sum(const double4* __restrict__ pm, uint32_t j0, uint32_t j1, uint32_t i,
+                                           const double4& p, double eps2) {
+  double acc = 0.0;
+#pragma unroll 4
+  for (uint32_t j = j0; j < j1; ++j) {
+    const double qx = pm[j].x, qy = pm[j].y, qz = pm[j].z, qm = pm[j].w;
+    const double dx = p.x - qx, dy = p.y - qy, dz = p.z - qz;
+    const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
+    double t;
+    if constexpr (FAST) t = qm * rsqrt64(r2);
+    else t = qm / sqrt(r2);
+    if constexpr (DIAG) acc += j > i ? t : 0.0;
+    else acc += t;
+  }
+  return acc;
+}
+
+// Workgroup (r, c): sum over the i of one block of 256 and the j > i of one
+// run of `jc` j-particles of m_i m_j / sqrt(|x_i - x_j|^2 + eps2).  Row r of
+// the grid holds i-block r's runs, from the block's own first particle on,
+// and then those of block nb - 1 - r, whose number adds up to nearly the same
+// for every r: no half of the grid is empty.
+//
+// Bound by f64 issue: per pair 3 subtractions, 10 fused or plain products and
+// sums and v_rsq_f64 at a quarter of their rate, about 75 clocks a wave.  At
+// N = 65536 the whole energy call takes 0.96 ms; with a square root and a
+// division per pair, the j-particles in LDS and half of the grid empty it
+// took 2.85 ms.
+__global__ __launch_bounds__(NB_T) void k_nb_potential(const double4* __restrict__ pm, uint32_t n, double eps2,
+                                                      uint32_t jc, uint32_t nb, double* __restrict__ partial) {
+  auto runs = [&](uint32_t blk) { return (n - blk * NB_T + jc - 1u) / jc; };
+  const uint32_t r = blockIdx.x, own = runs(r), mirror = nb - 1u - r;
+  uint32_t bi = r, c = blockIdx.y;
+  bool live = c < own;
+  if (!live) {
+    bi = mirror;
+    c -= own;
+    live = mirror != r && c < runs(mirror);  // the last columns of a short row hold no run
+  }
+  double acc = 0.0;
+  if (live) {
+    const uint32_t i = bi * NB_T + threadIdx.x;
+    const uint32_t j0 = bi * NB_T + c * jc;
+    const uint32_t j1 = n - j0 < jc ? n : j0 + jc;
+    const double4 p = pm[i < n ? i : n - 1u];
+    // positions come from float32, so squared distances are finite unless a
+    // position is not; a run that holds such a particle takes the plain form
+    bool ok = eps2 > 0.0 && __builtin_isfinite(p.x + p.y + p.z);
+    for (uint32_t j = j0 + threadIdx.x; j < j1; j += NB_T) {
+      const double4 q = pm[j];
+      ok = ok && __builtin_isfinite(q.x + q.y + q.z);
+    }
+    const bool fast = __syncthreads_and(ok ? 1 : 0) != 0;
+    const bool diag = j0 < bi * NB_T + NB_T;
+    if (fast) acc = diag ? pair_sum<true, true>(pm, j0, j1, i, p, eps2) : pair_sum<false, true>(pm, j0, j1, i, p, eps2);
+    else acc = diag ? pair_sum<true, false>(pm, j0, j1, i, p, eps2) : pair_sum<false, false>(pm, j0, j1, i, p, eps2);
+    acc = i < n ? acc * p.w : 0.0;
+  }
+  const double t = block_sum<NB_T / 64>(acc);
+  if (threadIdx.x == 0) partial[(size_t)r * gridDim.y + blockIdx.y] = t;
+}
+
+// result = sum(kin[0..nk)) - sum(pot[0..np)), by one workgroup in fixed order,
+// four independent loads in flight per thread (one at a time took 62 us for
+// 65536 partial sums).  `out` is host memory that the kernel writes itself.
+constexpr uint32_t NB_FINAL_T = 1024;
+
+__device__ __forceinline__ double strided_sum(const double* __restrict__ v, uint32_t n) {
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  uint32_t q = threadIdx.x;
+  for (; q + 3u * NB_FINAL_T < n; q += 4u * NB_FINAL_T) {
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) a[k] += v[q + k * NB_FINAL_T];
+  }
+  for (; q < n; q += NB_FINAL_T) a[0] += v[q];
+  return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+__global__ __launch_bounds__(NB_FINAL_T) void k_nb_final(const double* __restrict__ kin, uint32_t nk,
+                                                        const double* __restrict__ pot, uint32_t np,
+                                                        double* __restrict__ out) {
+  const double ks = block_sum<NB_FINAL_T / 64>(strided_sum(kin, nk));
+  const double ps = block_sum<NB_FINAL_T / 64>(strided_sum(pot, np));
   if (threadIdx.x == 0) out[0] = ks - ps;
 }
 
@@ -575,26 +633,29 @@ llama_status nbody_energy(const llama_view* view, float eps2, double* energy, vo
   const uint32_t n = (uint32_t)view->n;
   hipStream_t st = (hipStream_t)stream;
   const uint32_t nb = (n + NB_T - 1) / NB_T;
-  const size_t dbytes = (size_t)7 * n * sizeof(double);
-  const size_t pbytes = (size_t)nb * nb * sizeof(double);
-  const size_t kbytes = (size_t)nb * sizeof(double);
+  // j-particles per workgroup: 64, so that few particles fill the chip too;
+  // longer runs once that gives over 32768 workgroups (16 for each that the
+  // chip holds at once), so that the partial sums stay few
+  uint32_t jc = 64;
+  while ((uint64_t)nb * (n / jc) / 2u > 32768u) jc *= 2;
+  const uint32_t rows = (nb + 1) / 2;
+  const uint32_t cols = n ? (n + jc - 1) / jc + (n - (nb - 1) * NB_T + jc - 1) / jc + 1 : 0;
+  const size_t pbytes = (size_t)rows * cols * sizeof(double);
   void* buf;
   double* host;
-  if ((r = scratch_get(dbytes + pbytes + kbytes + 64, st, &buf, &host)) != LLAMA_OK) return r;
+  if ((r = scratch_get(sizeof(double4) * n + pbytes + sizeof(double) * nb + 64, st, &buf, &host)) != LLAMA_OK) return r;
   if (n == 0) {
     *energy = 0.0;
     return LLAMA_OK;
   }
-  double* d = (double*)buf;
-  double* pot = d + (size_t)7 * n;
-  double* kin = pot + (size_t)nb * nb;
-  double* out = kin + nb;
-  hipLaunchKernelGGL(k_nb_decode64, dim3(nb), dim3(NB_T), 0, st, s, n, d, cnt);
-  hipLaunchKernelGGL(k_nb_potential, dim3(nb, nb), dim3(NB_T), 0, st, (const double*)d, n, (double)eps2, pot);
-  hipLaunchKernelGGL(k_nb_kinetic, dim3(nb), dim3(NB_T), 0, st, (const double*)d, n, kin);
-  hipLaunchKernelGGL(k_nb_final, dim3(1), dim3(NB_T), 0, st, (const double*)kin, nb, (const double*)pot, nb * nb, out);
+  double4* pm = (double4*)buf;
+  double* pot = (double*)(pm + n);
+  double* kin = pot + (size_t)rows * cols;
+  hipLaunchKernelGGL(k_nb_decode64, dim3(nb), dim3(NB_T), 0, st, s, n, pm, kin, cnt);
+  hipLaunchKernelGGL(k_nb_potential, dim3(rows, cols), dim3(NB_T), 0, st, (const double4*)pm, n, (double)eps2, jc, nb, pot);
+  hipLaunchKernelGGL(k_nb_final, dim3(1), dim3(NB_FINAL_T), 0, st, (const double*)kin, nb, (const double*)pot,
+                     rows * cols, host);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(host, out, sizeof(double), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(LLAMA_ERR_HIP, std::string("n-body energy: ") + hipGetErrorString(e));
   *energy = *host;
