@@ -54,7 +54,8 @@ struct llama_view {
 namespace lm {
 
 enum PlanKind : uint32_t { PK_RAW = 0, PK_CONV = 1, PK_PACK = 2, PK_UNPACK = 3, PK_ZERO = 4, PK_XPOSE = 5, PK_MIXED = 6, PK_GENERIC = 7,
-                          PK_PACK_PLANAR = 8 };
+                          PK_PACK_PLANAR = 8,
+                          PK_TREE = 9 };
 
 struct Plan {
   PlanKind kind = PK_RAW;
@@ -68,6 +69,7 @@ struct Plan {
   MixArgs ma{};    // PK_MIXED
   GenArgs ga{};    // PK_GENERIC
   PlanarPackArgs pp{};  // PK_PACK_PLANAR
+  std::shared_ptr<TreeArgs> ta;  // PK_TREE
 };
 
 // Builds the device description of a view.  UNSUPPORTED when the tile
@@ -108,6 +110,10 @@ llama_status plan_mixed(const llama_view* src, const llama_view* dst, Plan& plan
 // through the destination mapping (computed mappings on both sides, integer
 // ChangeType, bit-packed codes up to 64 bits, bit-packed f16 / bf16).
 llama_status plan_generic(const llama_view* src, const llama_view* dst, Plan& plan);
+
+// The tiled form of a per-leaf or value-level copy: replaces `plan` when both
+// sides share one order and their AoSoA blocks fit a tile.
+void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan);
 
 // Geometry of one blob of a physical layout for Heatmap counting: records
 // come in periods of `period` bytes holding `recs` records each (AoS: one

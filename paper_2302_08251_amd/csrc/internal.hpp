@@ -222,6 +222,65 @@ struct GenArgs {
   uint8_t user_t[kMaxFields];    // scalar type of each leaf
 };
 
+// The tiled form of the per-leaf and value-level copies: a tile of the source
+// (whole AoS records and AoSoA blocks, runs of planes and streams) is brought
+// into LDS in contiguous segments, then every leaf moves from there to the
+// destination.
+enum TreeRead : uint32_t { TR_ZERO = 0, TR_ELEM = 1, TR_BYTES = 2, TR_BITS = 3 };
+enum TreeOp : uint32_t {
+  TO_MOVE = 0,   // the bits as they are
+  TO_INT32 = 1,  // integers of at most 32 bits on every side
+  TO_INT64 = 2,
+  TO_F32 = 3,    // f32 leaf: code, f16, bf16, f32 or f64 stored on either side
+  TO_F64 = 4,    // f64 leaf, codes of at most 32 bits
+  TO_GEN = 5,    // any float format pair
+};
+// How a float leaf is stored on one side of TO_F32 / TO_F64.
+enum TreeForm : uint32_t { TF_RAW = 0, TF_CODE = 1, TF_F16 = 2, TF_BF16 = 3, TF_F32 = 4, TF_F64 = 5 };
+
+struct TreeSeg {
+  const uint8_t* base;  // aligned down to 16 bytes
+  uint32_t lds;         // LDS slot; its low 4 bits: bytes between `base` and the data
+  uint32_t what;        // bits per record 13 | records per block (AoSoA) or 1, 13 | bytes of the
+                        // blob past the segment's last one, at most 16: 5
+};
+
+// One leaf, packed into words so that a wave reads it with scalar loads.
+//   side word: kind 2 | log2 of the stored element's bytes 2 | code or element
+//   bits 7 | E 4 | M 6 | TreeForm 3 | flag 1 | group 3 | blocks of several
+//   records (AoSoA) 1; the flag is sign-extension (source) or rounding to
+//   nearest even (destination)
+//   what: source column 8 | destination column 8 | TreeOp 4 | user type 4 |
+//   user bits 7 | user signed 1
+struct TreeLeaf {
+  uint32_t src, dst, what;
+  uint32_t lds;    // LDS address of the source's tile run | << 16: of the tile's stream words
+                   // (bit-packed destination) or of the leaf in the record image, else 0
+  uint32_t steps;  // bytes between records (inside a block: elements), source | destination << 16
+};
+
+struct TreeGroup {
+  uint32_t L;        // records per block
+  uint32_t block;    // bytes per block
+  uint32_t tstride;  // bytes from one tile to the next
+  uint32_t image;    // destination records put together in LDS: LDS address | first column << 16; else 0
+  Div div_L;
+};
+
+struct TreeArgs {
+  uint64_t n;
+  uint32_t tile, nseg, nleaf;
+  uint32_t images;               // 1: some leaf or group goes through an image
+  uint32_t img, img_bytes;       // LDS range of the stream words
+  TreeSeg seg[kMaxCols];
+  uint32_t scol[kMaxCols / 2];   // LDS address of each source column's tile run, two to a word
+  uint8_t* dcol[kMaxCols];
+  uint8_t* dleaf[kMaxFields];    // the leaf's first column
+  TreeGroup sg[kMaxGroups], dg[kMaxGroups];
+  TreeLeaf leaf[kMaxFields];
+};
+static_assert(sizeof(TreeArgs) <= 4096, "kernel arguments of a tiled per-leaf copy");
+
 // Pack of planes of 32-bit integers into BitPackedIntSoA streams, one plane
 // and one stream per field.
 struct PlanarPackArgs {
