@@ -813,6 +813,12 @@ llama_status plan_xpose(const llama_view* src, const llama_view* dst, Plan& plan
     return fail(LLAMA_ERR_UNSUPPORTED,
                 "a copy between views of different linearisation orders moves physical mappings only");
   if (S.rec_bytes != D.rec_bytes) return fail(LLAMA_ERR_RECORD_MISMATCH, "stored record sizes differ");
+  // records of one column are a plane in every layout
+  for (Side* x : {&S, &D})
+    if (x->ncols == 1) {
+      x->layout = LY_PLANAR;
+      x->mb = 1;
+    }
   // unit extents do not change either linearisation: drop them
   uint64_t e[8];
   uint32_t r = 0;
@@ -846,30 +852,42 @@ llama_status plan_xpose(const llama_view* src, const llama_view* dst, Plan& plan
     ++a.nmid;
   }
   const uint32_t U = std::min(S.cs, D.cs);
-  a.nunits = S.rec_bytes / U;
+  // tiles of one column (the wider side's) unless a side is record-major
+  const bool whole = S.layout == LY_AOS || D.layout == LY_AOS;
+  const uint32_t per = whole ? S.rec_bytes : std::max(S.cs, D.cs);  // bytes of a record in a tile
+  a.nunits = per / U;
+  a.nparts = S.rec_bytes / per;
   a.div_units = make_div(a.nunits);
-  // T x T records of the LDS image ([unit][q][p], rows of T + 1 units)
-  a.T = 32;
-  while (a.T > 4 && (uint64_t)S.rec_bytes * a.T * (a.T + 1) > kMaxTileLds) a.T >>= 1;
-  a.log2T = log2u(a.T);
-  a.src_rec_major = S.layout == LY_AOS ? 1u : 0u;
-  a.dst_rec_major = D.layout == LY_AOS ? 1u : 0u;
+  // Tile edges: runs of 256 bytes in memory, along Q in the source and along P
+  // in the destination, where a column's run has 64 records of 4 or 8 bytes
+  // and a record-major one 32 (of at least two columns); less where the tile
+  // then takes over 27000 bytes of LDS (six workgroups a CU: over 11 copies
+  // 468 us in all, with 40960 478, with longer runs and 53000 545) or where
+  // there are too few tiles to fill the chip
+  auto edge = [&](const Side& x) -> uint32_t { return x.layout == LY_AOS ? 5u : U >= 4u ? 6u : 7u; };
+  a.log2Q = edge(S);
+  a.log2P = edge(D);
+  auto lds_of = [&] { return ((uint64_t)per << a.log2Q) * ((1u << a.log2P) + xpose_pad(U)); };
+  auto shrink = [&] { --(a.log2P >= a.log2Q ? a.log2P : a.log2Q); };
+  while (lds_of() > 27000 && (a.log2P > 3 || a.log2Q > 3)) shrink();
+  while ((src->n * a.nparts) >> (a.log2P + a.log2Q) < 1024 && (a.log2P > 4 || a.log2Q > 4)) shrink();
   auto lmag = [](const Side& x) -> uint64_t {
     if (x.layout != LY_AOSOA || (x.lanes & (x.lanes - 1)) == 0) return 0;
     return ~0ull / x.lanes + 1ull;  // ceil(2^64 / L) for L not a power of two
   };
   a.src_lmag = lmag(S);
   a.dst_lmag = lmag(D);
-  a.nPt = (a.eP + a.T - 1) / a.T;
-  a.nQt = (a.eQ + a.T - 1) / a.T;
+  a.nPt = (a.eP + (1u << a.log2P) - 1) >> a.log2P;
+  a.nQt = (a.eQ + (1u << a.log2Q) - 1) >> a.log2Q;
   uint64_t M = 1;
   for (uint32_t k = 0; k < a.nmid; ++k) M *= a.mext[k];
-  a.ntiles = M * a.nPt * a.nQt;
+  a.ntiles = M * a.nPt * a.nQt * a.nparts;
   plan.kind = PK_XPOSE;
   plan.unit = U;
   plan.ntiles = a.ntiles;
-  plan.grid = (uint32_t)std::min<uint64_t>(a.ntiles, 1u << 20);
-  plan.lds = (uint32_t)(((uint64_t)S.rec_bytes * a.T * (a.T + 1) + 15u) & ~15ull);
+  plan.grid = (uint32_t)std::min<uint64_t>(a.ntiles, 1u << 24);
+  a.xcd = plan.grid == a.ntiles ? 1u : 0u;
+  plan.lds = (uint32_t)((lds_of() + 15u) & ~15ull);
   plan.alg_bytes = mapped_bytes(src->rec, src->map, src->n) + mapped_bytes(dst->rec, dst->map, dst->n);
   return LLAMA_OK;
 }

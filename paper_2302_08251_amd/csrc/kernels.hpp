@@ -251,6 +251,8 @@ hipError_t launch_conv(const TileArgs& a, uint32_t unit, uint32_t grid, uint32_t
 hipError_t launch_pack(const TileArgs& a, uint32_t grid, uint32_t lds, hipStream_t st);
 hipError_t launch_unpack(const TileArgs& a, uint32_t unit, uint32_t grid, uint32_t lds, hipStream_t st);
 hipError_t launch_zero(const TileArgs& a, uint32_t unit, uint32_t grid, hipStream_t st);
+// units past a tile row in LDS: consecutive rows then start a bank apart
+constexpr uint32_t xpose_pad(uint32_t unit) { return unit >= 4u ? 1u : 4u / unit; }
 hipError_t launch_xpose(const XposeArgs& a, uint32_t unit, uint32_t grid, uint32_t lds, hipStream_t st);
 hipError_t launch_mixed(const MixArgs& a, uint32_t grid, hipStream_t st);
 hipError_t launch_generic(const GenArgs& a, uint32_t grid, hipStream_t st);
