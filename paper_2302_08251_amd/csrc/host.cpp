@@ -597,11 +597,17 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
     return merge_aos && (t / 4u) * F <= (uint64_t)merge_in_place_items(ES) * kThreads;
   };
   // pack: the tile's stream-word image (t * B / 8 bytes per field), unless
-  // every field's codes go from registers straight to the stream (planes of
-  // 4-byte values whose tile runs start on the 16-byte grid, B a multiple of 8)
+  // every field's codes go from registers straight to the stream (columns of
+  // 4-byte values, B a multiple of 8)
   const bool pack = plan.kind == PK_PACK;
-  const bool pack_direct = pack && S.layout == LY_PLANAR && S.cs == 4 && S.es == 4 && (S.mb || (S.n & 3u) == 0) &&
-                           (D.bits & 7u) == 0;
+  const bool pack_direct = pack && S.cs == 4 && S.es == 4 && (D.bits & 7u) == 0;
+  // unpack into AoS records of 4-byte leaves: an LDS image of the tile's
+  // records, where it fits (explicit tiles may leave no room: gathered then)
+  const bool unpack_aos = plan.kind == PK_UNPACK && D.layout == LY_AOS && D.cs == 4 && D.es == 4;
+  auto unpack_lds = [&](uint64_t t) {
+    return ((tile_lds_bytes(S, (uint32_t)t) + 15u) & ~15ull) + t * (uint64_t)D.rec_bytes;
+  };
+  auto unpack_image = [&](uint64_t t) { return unpack_aos && unpack_lds(t) <= kMaxTileLds; };
   auto lds_total = [&](uint64_t t) -> uint64_t {
     // line-owner copies build the destination's runs in registers from the
     // tile's source image (and halo), the only LDS image (+16: a misaligned
@@ -609,6 +615,7 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
     if (line) return tile_lds_bytes(S, (uint32_t)(t + halo_lds)) + 16u;
     const uint64_t a = tile_lds_bytes(S, (uint32_t)t);
     if (pack_direct) return a;
+    if (unpack_image(t)) return unpack_lds(t);
     if (pack) return ((a + 15u) & ~15ull) + (uint64_t)D.ncols * (t * D.bits / 8u);
     if (in_place(t)) return a;
     return canonical ? ((a + 15u) & ~15ull) + can_bytes(t) : a;
@@ -635,10 +642,14 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
     const bool unpack = plan.kind == PK_UNPACK;
     // direct packs: 16 KiB, 24 KiB for 8-bit codes (measured on 256 Mi
     // values: 4096 beat 6144 by 2-6 % at B = 16, 24, 32; 6144 beat 4096 by
-    // 20 % at B = 8).  Word-image packs: about 32 KiB with the image, see below.
-    const uint64_t target = pack_direct ? (D.bits == 8 ? 24576 : 16384) : pack ? 32768
+    // 20 % at B = 8) and for several fields, whose quads then fill the waves
+    // (4 Mi records of 7 fields, 24 bits: from planes 37.2 us with 16 KiB, 36.3
+    // with 24, 37.1 with 32).  Word-image packs: about 32 KiB with the image,
+    // see below.  Unpacks of several 4-byte fields: 12 KiB of stream words
+    // (8 KiB 42.4 us into AoS, 12 KiB 37.5, 16 KiB with longer output tiles 39.7).
+    const uint64_t target = pack_direct ? (D.bits == 8 || S.ncols > 1 ? 24576 : 16384) : pack ? 32768
                             : line ? (D.cs == 1 && S.cs > 1 ? 32768 : 24576)  // the tile and its halo
-                            : unpack ? 8192
+                            : unpack ? (S.ncols > 1 && D.es == 4 ? 12288 : 8192)
                             // ChangeType: 32 KiB on the wider side; f32 -> f16 / bf16
                             // 16 KiB (measured on planes: 4096 values beat 8192 by 5-8 %)
                             : plan.kind == PK_CONV ? (S.es == 4 && D.es == 2 ? 16384 : 32768)
@@ -648,7 +659,7 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
                             : (bs && bd) ? 24576
                             : (bs || bd) ? 30720
                                          : 16384;
-    uint64_t per = plan.kind == PK_UNPACK ? lds_total(gran) : std::max<uint64_t>(lds_total(gran), gran * dst_bytes);
+    uint64_t per = plan.kind == PK_UNPACK ? tile_lds_bytes(S, (uint32_t)gran) : std::max<uint64_t>(lds_total(gran), gran * dst_bytes);
     uint64_t k = per ? (target / per) : 1;
     if (k < 1) k = 1;
     const uint64_t dst_cap = unpack ? 16384 : 65536;
@@ -757,8 +768,8 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
       plan.args.can_off = (uint32_t)((tile_lds_bytes(S, (uint32_t)tile) + 15u) & ~15u);
     }
   }
-  // can_off 0: no word image (every field stored directly)
-  if (pack && !pack_direct) plan.args.can_off = (uint32_t)((tile_lds_bytes(S, (uint32_t)tile) + 15u) & ~15u);
+  // can_off 0: no word image (every field stored directly), no record image
+  if ((pack && !pack_direct) || unpack_image(tile)) plan.args.can_off = (uint32_t)((tile_lds_bytes(S, (uint32_t)tile) + 15u) & ~15u);
   plan.args.tile = (uint32_t)tile;
   plan.ntiles = (src->n + tile - 1) / tile;
   if (plan.ntiles > 0xFFFFFFFFull) return fail(LLAMA_ERR_INDEX_OVERFLOW, "too many tiles");

@@ -1678,14 +1678,17 @@ __device__ __forceinline__ void store_conv(const Side& s, const Side& d, uint64_
 
 // ---------------------------------------------------------------------------
 // Phase B, pack into bit streams (Sec. 3 bit-packed SoA).  Every value of the
-// tile is encoded exactly once.  A lane takes four consecutive values of an
-// element plane (one 16-byte LDS read) and writes their codes into an LDS
-// image of the tile's stream words: with B = 8, 16 or 32 the four codes fill
-// whole words of their own, which are stored plainly; otherwise the codes
-// (as one group for B <= 8, two pairs for B <= 16, singly above) are ORed in
-// with LDS atomics, since a word's bits may come from two lanes.  The image
-// starts zeroed, so the bits past the last value stay zero, and goes out with
-// 16-byte stores: a wave writes 1 KiB contiguous per store.
+// tile is encoded exactly once.  A lane takes four consecutive values of a
+// column (one 16-byte LDS read from a plane on the 16-byte grid, four reads from
+// records, whose stride costs a four-way bank conflict at most times).  With B
+// a multiple of 8 the four codes fill whole words, which go to the stream from
+// registers; otherwise they (as one group for B < 8, two pairs for B < 16,
+// singly above) are ORed into an LDS image of the tile's stream words with LDS
+// atomics, since a word's bits may come from two lanes.  The image starts
+// zeroed, so the bits past the last value stay zero, and goes out with 16-byte
+// stores: a wave writes 1 KiB contiguous per store.  4 Mi records of 7 x f32 to
+// 24-bit codes: from AoS 35 us (5.6 TB/s), value by value through the image 52;
+// from planes 36 us, one field after another by the whole workgroup 56.
 // ---------------------------------------------------------------------------
 
 // Float formats that get a compile-time encoder (any other goes through the
@@ -1766,66 +1769,76 @@ __device__ __forceinline__ void pack_quad_words(const uint32_t (&c)[4], uint32_t
   }
 }
 
-// Codes of a plane of 4-byte values straight from registers to the stream
-// (B = 8 * NWQ): a lane encodes four consecutive values from one 16-byte LDS
-// read and stores their NWQ whole words, so a wave writes 64 * NWQ * 4
-// contiguous bytes per store.  Full quads need no checks; the tile's last,
-// partial quad is written by one lane, word by word up to the stream's end.
-template <int NWQ, int CODEC, int FMT>
-__device__ __forceinline__ void pack_direct(const uint8_t* plane, uint32_t nt, uint32_t nw,
-                                            __amdgpu_buffer_rsrc_t rs, const Side& d) {
-  const uint32_t full = nt >> 2;
-#pragma unroll 2
-  for (uint32_t q = threadIdx.x; q < full; q += blockDim.x) {
-    const u32x4 v = *(const u32x4*)(plane + 16u * q);
-    uint32_t c[4], w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) c[k] = encode_fmt<CODEC, FMT>(v[k], d);
-    pack_quad_words<NWQ>(c, w);
-    const uint32_t off = 4u * NWQ * q;  // the quad's first word
-    if constexpr (NWQ == 1) __builtin_amdgcn_raw_buffer_store_b32(w[0], rs, off, 0, kStoreNT);
-    else if constexpr (NWQ == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2{w[0], w[1]}, rs, off, 0, kStoreNT);
-    else if constexpr (NWQ == 3) __builtin_amdgcn_raw_buffer_store_b96(u32x3{w[0], w[1], w[2]}, rs, off, 0, kStoreNT);
-    else __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[0], w[1], w[2], w[3]}, rs, off, 0, kStoreNT);
-  }
-  if ((nt & 3u) && threadIdx.x == 0) {
-    const u32x4 v = *(const u32x4*)(plane + 16u * full);
-    uint32_t c[4], w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) c[k] = 4u * full + k < nt ? encode_fmt<CODEC, FMT>(v[k], d) : 0u;
-    pack_quad_words<NWQ>(c, w);
-    for (uint32_t k = 0; k < (uint32_t)NWQ && NWQ * full + k < nw; ++k)
-      __builtin_amdgcn_raw_buffer_store_b32(w[k], rs, 4u * (NWQ * full + k), 0, 0);
+// Work items of the quad loops below: a wave takes 64 quads (four consecutive
+// records each) of one field at a time, the fields' groups in turn over the
+// waves.  (With the whole workgroup on one field after another, tiles of many
+// fields, which hold few quads of each, left most lanes idle.)
+template <typename Body>
+__device__ __forceinline__ void for_quads(uint32_t F, uint32_t nt, Body&& body) {
+  const uint32_t quads = (nt + 3u) >> 2, gpf = (quads + 63u) >> 6;
+  const Div dg = make_div_dev(gpf);
+  const uint32_t items = F * gpf, nw = num_waves();
+  for (uint32_t it = wave_id(); it < items; it += nw) {
+    const uint32_t f = fdiv(it, dg);
+    const uint32_t q = (it - f * gpf) * 64u + lane_id();
+    if (q < quads) body(f, q);
   }
 }
 
-// Codes of a plane of 4-byte values into the tile's stream-word image, four
-// consecutive values per lane.  CLS 0: B = 8, 16 or 32 (whole words, plain
-// LDS stores); CLS 1: B < 8 (the four codes as one group); CLS 2: B < 16 (two
-// pairs); CLS 3: B < 32 (one by one).  Groups that may share a word with
-// another lane's are ORed in with LDS atomics (a group spans at most two
-// words).  Values past the tile give code 0.  (Assembling whole words in
-// registers with one ds_bpermute carry per lane, so that every word has one
+// Codes of four consecutive 4-byte values of field f straight from registers
+// to the stream (B = 8 * NWQ): the quad's codes are NWQ whole words, so a wave
+// writes 64 * NWQ * 4 contiguous bytes per store.  The tile's last, partial
+// quad goes out word by word up to the stream's end.
+template <int NWQ, int CODEC, int FMT, int SL>
+__device__ __forceinline__ void pack_direct(const Side& s, const Side& d, uint64_t i0, uint32_t nt, uint32_t nw,
+                                            const uint8_t* lds) {
+  for_quads(d.ncols, nt, [&](uint32_t f, uint32_t q) {
+    const uint64_t start = seg_start<LY_STREAM>(d, f, i0);
+    const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_STREAM>(d, f) + start, d.blob_size - start);
+    uint32_t v[4], c[4], w[4];
+    read_elems4<4, SL>(s, lds, 4u * q, f, v);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = encode_fmt<CODEC, FMT>(v[k], d);
+    const uint32_t off = 4u * NWQ * q;  // the quad's first word
+    if (4u * q + 4u <= nt) {
+      pack_quad_words<NWQ>(c, w);
+      if constexpr (NWQ == 1) __builtin_amdgcn_raw_buffer_store_b32(w[0], rs, off, 0, kStoreNT);
+      else if constexpr (NWQ == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2{w[0], w[1]}, rs, off, 0, kStoreNT);
+      else if constexpr (NWQ == 3) __builtin_amdgcn_raw_buffer_store_b96(u32x3{w[0], w[1], w[2]}, rs, off, 0, kStoreNT);
+      else __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[0], w[1], w[2], w[3]}, rs, off, 0, kStoreNT);
+    } else {
+#pragma unroll
+      for (int k = 1; k < 4; ++k) c[k] = 4u * q + k < nt ? c[k] : 0u;
+      pack_quad_words<NWQ>(c, w);
+      for (uint32_t k = 0; k < (uint32_t)NWQ && NWQ * q + k < nw; ++k)
+        __builtin_amdgcn_raw_buffer_store_b32(w[k], rs, off + 4u * k, 0, 0);
+    }
+  });
+}
+
+// Codes of 4-byte values into the tile's stream-word image, four consecutive
+// values of a field per lane.  CLS 1: B < 8 (the four codes as one group);
+// CLS 2: B < 16 (two pairs); CLS 3: B < 32 (one by one).  Groups that may share
+// a word with another lane's are ORed in with LDS atomics (a group spans at
+// most two words).  Values past the tile give code 0.  (Assembling whole words
+// in registers with one ds_bpermute carry per lane, so that every word has one
 // plain writer, measured 7 % slower than the atomics.)
-template <int CLS, int CODEC, int FMT>
-__device__ __forceinline__ void pack_image(const uint8_t* plane, uint32_t nt, uint32_t B, uint32_t* wf,
-                                           const Side& d) {
-  const uint32_t quads = (nt + 3u) >> 2;
-  for (uint32_t q = threadIdx.x; q < quads; q += blockDim.x) {
-    const u32x4 v = *(const u32x4*)(plane + 16u * q);
+template <int CLS, int CODEC, int FMT, int SL>
+__device__ __forceinline__ void pack_image(const Side& s, const Side& d, uint32_t nt, const uint8_t* lds,
+                                           uint32_t* words, uint32_t wstride) {
+  const uint32_t B = d.bits;
+  for_quads(d.ncols, nt, [&](uint32_t f, uint32_t q) {
+    uint32_t* wf = words + f * wstride;
     const uint32_t r = 4u * q;
-    uint32_t c[4];
+    uint32_t v[4], c[4];
+    read_elems4<4, SL>(s, lds, r, f, v);
 #pragma unroll
     for (int k = 0; k < 4; ++k) c[k] = encode_fmt<CODEC, FMT>(v[k], d);
     if (r + 4u > nt) {
 #pragma unroll
       for (int k = 1; k < 4; ++k) c[k] = r + k < nt ? c[k] : 0u;
     }
-    if constexpr (CLS == 0) {
-      if (B == 8u) wf[q] = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-      else if (B == 16u) *(u32x2*)(wf + 2u * q) = u32x2{c[0] | (c[1] << 16), c[2] | (c[3] << 16)};
-      else *(u32x4*)(wf + 4u * q) = u32x4{c[0], c[1], c[2], c[3]};
-    } else if constexpr (CLS == 1) {
+    if constexpr (CLS == 1) {
       or_bits(wf, r * B, c[0] | (c[1] << B) | (c[2] << (2u * B)) | (c[3] << (3u * B)), 4u * B);
     } else if constexpr (CLS == 2) {
       or_bits(wf, r * B, c[0] | (c[1] << B), 2u * B);
@@ -1834,7 +1847,7 @@ __device__ __forceinline__ void pack_image(const uint8_t* plane, uint32_t nt, ui
 #pragma unroll
       for (int k = 0; k < 4; ++k) or_bits(wf, r * B + k * B, c[k], B);
     }
-  }
+  });
 }
 
 template <int CODEC, int FMT, int SL>
@@ -1844,60 +1857,37 @@ __device__ __forceinline__ void store_pack(const Side& s, const Side& d, uint64_
   const uint32_t B = d.bits;
   const uint32_t F = d.ncols;
   const uint32_t nw = (nt * B + 31u) >> 5;  // stream words of this tile
-  // element planes of 4-byte values on the 16-byte grid (not Bytesplit byte
-  // planes) are read four values at a time; with B a multiple of 8 their
-  // codes bypass the word image
-  auto quad_plane = [&](uint32_t f) {
-    return SL == LY_PLANAR && ES == 4 && s.cs == 4u && (planar_phase(s, f) & 15u) == 0u;
-  };
-  auto direct = [&](uint32_t f) { return quad_plane(f) && (B & 7u) == 0u; };
-  bool imaged = false;  // some field went through the word image
-  for (uint32_t f = 0; f < F; ++f) {
-    uint32_t* wf = words + f * wstride;
-    if constexpr (SL == LY_PLANAR && ES == 4) {
-      if (direct(f)) {
-        // B = 8, 16, 24, 32: the four codes of a quad are B / 8 whole words
-        // starting on a word boundary, so they go from registers straight to
-        // the stream (a wave writes 64 * B / 2 contiguous bytes per store, whole
-        // 128-byte lines); no word image, no barrier.  Only the tile's last
-        // quad may hold words past the stream, which are dropped word by word.
-        const uint8_t* plane = lds + f * s.lds_stride;
-        const uint64_t start = seg_start<LY_STREAM>(d, f, i0);
-        const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_STREAM>(d, f) + start, d.blob_size - start);
+  if constexpr (ES == 4) {
+    // columns of 4-byte values (not Bytesplit byte columns): four values at a time
+    if (s.cs == 4u) {
+      if ((B & 7u) == 0u) {  // whole words, no image (the plan allots none)
         constexpr uint32_t FB = 1u + PackFmtInfo<FMT>::E + PackFmtInfo<FMT>::M;  // a fixed format's code bits
         if constexpr (FMT != PF_RUNTIME && FB % 8u == 0u) {
-          pack_direct<FB / 8u, CODEC, FMT>(plane, nt, nw, rs, d);
+          pack_direct<FB / 8u, CODEC, FMT, SL>(s, d, i0, nt, nw, lds);
         } else {
-          switch (B) {  // block-uniform, once per field
-            case 8u: pack_direct<1, CODEC, FMT>(plane, nt, nw, rs, d); break;
-            case 16u: pack_direct<2, CODEC, FMT>(plane, nt, nw, rs, d); break;
-            case 24u: pack_direct<3, CODEC, FMT>(plane, nt, nw, rs, d); break;
-            default: pack_direct<4, CODEC, FMT>(plane, nt, nw, rs, d); break;
+          switch (B) {  // block-uniform
+            case 8u: pack_direct<1, CODEC, FMT, SL>(s, d, i0, nt, nw, lds); break;
+            case 16u: pack_direct<2, CODEC, FMT, SL>(s, d, i0, nt, nw, lds); break;
+            case 24u: pack_direct<3, CODEC, FMT, SL>(s, d, i0, nt, nw, lds); break;
+            default: pack_direct<4, CODEC, FMT, SL>(s, d, i0, nt, nw, lds); break;
           }
         }
-        continue;
+        return;
       }
-      if (quad_plane(f)) {
-        imaged = true;
-        const uint8_t* plane = lds + f * s.lds_stride;
-        // the code-width class is block-uniform: one loop per class, no
-        // width branches inside
-        if (B == 8u || B == 16u || B == 32u) pack_image<0, CODEC, FMT>(plane, nt, B, wf, d);
-        else if (B < 8u) pack_image<1, CODEC, FMT>(plane, nt, B, wf, d);
-        else if (B < 16u) pack_image<2, CODEC, FMT>(plane, nt, B, wf, d);
-        else pack_image<3, CODEC, FMT>(plane, nt, B, wf, d);
-        continue;
-      }
+      // the code-width class is block-uniform: no width branches inside the loops
+      if (B < 8u) pack_image<1, CODEC, FMT, SL>(s, d, nt, lds, words, wstride);
+      else if (B < 16u) pack_image<2, CODEC, FMT, SL>(s, d, nt, lds, words, wstride);
+      else pack_image<3, CODEC, FMT, SL>(s, d, nt, lds, words, wstride);
     }
-    imaged = true;
-    for (uint32_t r = threadIdx.x; r < nt; r += blockDim.x)
-      or_bits(wf, r * B, encode_fmt<CODEC, FMT>(fetch_elem<ES, SL>(s, lds, r, f), d), B);
   }
-  if (!imaged) return;  // block-uniform: every field went out directly
+  if (ES != 4 || s.cs != 4u) {
+    for (uint32_t f = 0; f < F; ++f)
+      for (uint32_t r = threadIdx.x; r < nt; r += blockDim.x)
+        or_bits(words + f * wstride, r * B, encode_fmt<CODEC, FMT>(fetch_elem<ES, SL>(s, lds, r, f), d), B);
+  }
   __syncthreads();
   const uint32_t nch = (nw + 3u) >> 2;
   for (uint32_t f = 0; f < F; ++f) {
-    if (direct(f)) continue;
     // tiles are multiples of 128 records, so every tile's stream starts 16-byte aligned
     const uint64_t start = seg_start<LY_STREAM>(d, f, i0);
     const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_STREAM>(d, f) + start, d.blob_size - start);
@@ -1919,40 +1909,54 @@ __device__ __forceinline__ void store_pack(const Side& s, const Side& d, uint64_
 // Phase B, unpack from bit streams into a physical layout
 // ---------------------------------------------------------------------------
 
-// Unpack into element planes of 4-byte values: a lane decodes four
-// consecutive values of one field straight from the stream words and stores
-// them as one 16-byte chunk (a wave writes 1 KiB contiguous).  Used when the
-// plane's tile run starts on the 16-byte grid; the generic gather below
-// handles every other destination.
-template <int CODEC>
-__device__ __forceinline__ void store_unpack_planar4(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
-                                                     const uint8_t* lds, uint32_t f) {
+// Unpack of 4-byte values, four consecutive records of a field per lane,
+// decoded straight from the stream words.  Planes and AoSoA blocks of a
+// multiple of four records: the quad is one 16-byte store (a wave writes whole
+// lines; planes may start at any element).  AoS: the quads are put into an LDS
+// image of the tile's records, which then leaves in 16-byte stores.  4 Mi
+// records of 7 x f32 from 24-bit codes: into AoS 37.5 us (5.2 TB/s), gathered
+// unit by unit 44; into planes 35 us, one field after another 48 (off the
+// 16-byte grid, gathered, 61).
+template <int CODEC, int DL>
+__device__ __forceinline__ void store_unpack_quads(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
+                                                   const uint8_t* lds, uint8_t* img) {
   const uint32_t B = s.bits;
-  const uint32_t quads = (nt + 3u) >> 2;
-  const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
-  const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start);
-  const uint8_t* plane = lds + f * s.lds_stride;
-  for (uint32_t q = threadIdx.x; q < quads; q += blockDim.x) {
+  for_quads(d.ncols, nt, [&](uint32_t f, uint32_t q) {
+    const uint8_t* plane = lds + f * s.lds_stride;
     const uint32_t r = 4u * q;
     uint32_t v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = (uint32_t)decode<CODEC>(stream_code(plane, r + k, B), s);
-    if (r + 4u <= nt) {
-      __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0], v[1], v[2], v[3]}, rs, 16u * q, 0, kStoreNT);
+    if constexpr (DL == LY_AOS) {
+      uint8_t* to = img + r * d.rec_bytes + 4u * f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) *(uint32_t*)(to + k * d.rec_bytes) = v[k];
     } else {
-      for (uint32_t k = 0; r + k < nt; ++k) __builtin_amdgcn_raw_buffer_store_b32(v[k], rs, 16u * q + 4u * k, 0, 0);
+      const void* blob = (DL == LY_PLANAR && d.mb) ? d.blob[f] : d.blob[0];
+      const uint64_t base = col_base<DL>(d, i0, f);
+      const auto rs = make_rsrc((const uint8_t*)blob + base, d.blob_size - base);
+      const uint32_t off = col_local<DL>(d, r);
+      if (r + 4u <= nt) {
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0], v[1], v[2], v[3]}, rs, off, 0, kStoreNT);
+      } else {
+        for (uint32_t k = 0; r + k < nt; ++k) __builtin_amdgcn_raw_buffer_store_b32(v[k], rs, off + 4u * k, 0, 0);
+      }
     }
+  });
+  if constexpr (DL == LY_AOS) {
+    __syncthreads();
+    store_identity<4>(d, d, i0, nt, img);
   }
 }
 
+// img: the LDS record image of an AoS destination of 4-byte leaves, or null
+// where the plan found no room for it.
 template <int CODEC, int U, int DL>
 __device__ __forceinline__ void store_unpack(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
-                                             const uint8_t* lds) {
-  if constexpr (DL == LY_PLANAR && U == 4 && CodecInfo<CODEC>::ES == 4) {
-    // every field's run must start on the 16-byte grid (single-blob planes
-    // start at f * 4n)
-    if (d.mb || (d.n & 3u) == 0u) {
-      for (uint32_t f = 0; f < d.ncols; ++f) store_unpack_planar4<CODEC>(s, d, i0, nt, lds, f);
+                                             const uint8_t* lds, uint8_t* img) {
+  if constexpr (U == 4 && CodecInfo<CODEC>::ES == 4) {
+    if (DL == LY_PLANAR || (DL == LY_AOS && img) || (DL == LY_AOSOA && (d.lanes & 3u) == 0u)) {
+      store_unpack_quads<CODEC, DL>(s, d, i0, nt, lds, img);
       return;
     }
   }
