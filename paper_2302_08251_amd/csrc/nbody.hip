@@ -8,6 +8,7 @@
 // ChangeType(F64 -> F32, physical), BitPackedFloatSoA with E <= 8, M <= 23
 // (codes decode exactly to float32).  Compute and accumulation are FP32;
 // only the energy check runs in FP64.
+#include <algorithm>
 #include <mutex>
 
 #include "host.hpp"
@@ -148,6 +149,9 @@ __device__ __forceinline__ void nb_count(const NbCount& c, const Side& s, uint32
 // Update: partial accelerations of i-block blockIdx.x over j-slice blockIdx.y
 // ---------------------------------------------------------------------------
 
+// COUNT: the view is instrumented (without the counting code the kernel keeps
+// its scalars in registers and starts sooner).
+template <bool COUNT>
 __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, float eps2, uint32_t per_slice,
                                                    float* __restrict__ part, const NbCount cnt) {
   __shared__ JTile tile;
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
     zi = nb_load(s, i, 2);
   }
   // counted once per particle: in the first slice of each i-block
-  const bool counting = cnt.fac || cnt.heat[0];
+  const bool counting = COUNT && (cnt.fac || cnt.heat[0]);
   if (counting && blockIdx.y == 0)
     for (uint32_t f = 0; f < 3; ++f) nb_count(cnt, s, f, 0, i, i < n);
   uint32_t jloads = 0;  // j-tile loads of this thread (each of leaves 0, 1, 2, 6)
@@ -191,8 +195,10 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
     tile.store<6>(me, pm);
     __syncthreads();
     float tx = 0.f, ty = 0.f, tz = 0.f;
+    // the tile's particles, a short last tile in groups of 8 (mass 0 past its end)
+    const uint32_t in_tile = j1 - jt < NB_T ? (j1 - jt + 7u) & ~7u : NB_T;
 #pragma unroll 8
-    for (uint32_t k = 0; k < NB_T; ++k) {
+    for (uint32_t k = 0; k < in_tile; ++k) {
       const uint16_t kk = (uint16_t)k;
       const float qx = tile.load<0>(kk), qy = tile.load<1>(kk), qz = tile.load<2>(kk), qm = tile.load<6>(kk);
       const float dx = qx - xi, dy = qy - yi, dz = qz - zi;
@@ -215,7 +221,7 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
     p[n + i] = ay;
     p[2u * n + i] = az;
   }
-  if (cnt.fac) {
+  if (COUNT && cnt.fac) {
     nb_fac_add(cnt, 0, jloads);
     nb_fac_add(cnt, 2, jloads);
     nb_fac_add(cnt, 4, jloads);
@@ -223,22 +229,30 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
   }
 }
 
+// Sum of the slices' accelerations in fixed order, compensated (Kahan): the
+// number of slices then does not show in the result.
 __device__ __forceinline__ void nb_accel(const float* __restrict__ part, uint32_t n, uint32_t slices, uint32_t i,
-                                         float& ax, float& ay, float& az) {
-  ax = ay = az = 0.f;
-  for (uint32_t sl = 0; sl < slices; ++sl) {  // fixed order: deterministic
+                                         float (&a)[3]) {
+  float c[3] = {0.f, 0.f, 0.f};
+  a[0] = a[1] = a[2] = 0.f;
+#pragma unroll 8
+  for (uint32_t sl = 0; sl < slices; ++sl) {
     const float* p = part + (size_t)sl * 3u * n;
-    ax += p[i];
-    ay += p[n + i];
-    az += p[2u * n + i];
+#pragma unroll
+    for (uint32_t k = 0; k < 3; ++k) {
+      const float y = p[k * n + i] - c[k], t = a[k] + y;
+      c[k] = (t - a[k]) - y;
+      a[k] = t;
+    }
   }
 }
 
 // Kick (v += dt a) then drift (x += dt v as stored), physical storage.
+template <bool COUNT>
 __global__ __launch_bounds__(NB_T) void k_nb_kick_drift(const Side s, uint32_t n, float dt, uint32_t slices,
                                                        const float* __restrict__ part, const NbCount cnt) {
   const uint32_t i = blockIdx.x * NB_T + threadIdx.x;
-  if (cnt.fac || cnt.heat[0]) {  // vel loaded and stored, then pos loaded and stored
+  if (COUNT && (cnt.fac || cnt.heat[0])) {  // vel loaded and stored, then pos loaded and stored
     for (uint32_t c = 0; c < 3; ++c) {
       nb_count(cnt, s, 3 + c, 0, i, i < n);
       nb_count(cnt, s, 3 + c, 1, i, i < n);
@@ -248,7 +262,7 @@ __global__ __launch_bounds__(NB_T) void k_nb_kick_drift(const Side s, uint32_t n
   }
   if (i >= n) return;
   float a[3];
-  nb_accel(part, n, slices, i, a[0], a[1], a[2]);
+  nb_accel(part, n, slices, i, a);
 #pragma unroll
   for (uint32_t c = 0; c < 3; ++c) {
     const float v = __builtin_fmaf(dt, a[c], nb_load(s, i, 3 + c));
@@ -261,13 +275,14 @@ __global__ __launch_bounds__(NB_T) void k_nb_kick_drift(const Side s, uint32_t n
 // Kick and drift for bit-packed streams: codes of a 256-particle tile are
 // staged in LDS and the stream words (a tile is a whole number of words)
 // are assembled and stored by one lane each.
+template <bool COUNT>
 __global__ __launch_bounds__(NB_T) void k_nb_kick_drift_stream(const Side s, uint32_t n, float dt,
                                                               uint32_t slices, const float* __restrict__ part,
                                                               const NbCount cnt) {
   __shared__ uint32_t codes[6][NB_T];
   const uint32_t i0 = blockIdx.x * NB_T;
   const uint32_t i = i0 + threadIdx.x;
-  if (cnt.fac)
+  if (COUNT && cnt.fac)
     for (uint32_t f = 0; f < 6; ++f) {  // every position and velocity code loaded once and stored once
       nb_fac_add(cnt, 2u * f, i < n ? 1u : 0u);
       nb_fac_add(cnt, 2u * f + 1u, i < n ? 1u : 0u);
@@ -276,7 +291,7 @@ __global__ __launch_bounds__(NB_T) void k_nb_kick_drift_stream(const Side s, uin
   const uint32_t E = s.exp_bits, M = s.man_bits, B = s.bits;
   if (i < n) {
     float a[3];
-    nb_accel(part, n, slices, i, a[0], a[1], a[2]);
+    nb_accel(part, n, slices, i, a);
 #pragma unroll
     for (uint32_t c = 0; c < 3; ++c) {
       const float v = __builtin_fmaf(dt, a[c], nb_load(s, i, 3 + c));
@@ -545,16 +560,37 @@ llama_status nb_side(const llama_view* vin, Side& s, NbCount& cnt) {
   return LLAMA_OK;
 }
 
-uint32_t nb_slices(uint32_t n) {
-  // enough workgroups to fill 256 CUs several times over
+// The j range's division: slices of `per` j-particles (a multiple of 64).
+// Workgroups are spread over the CUs, so a step takes as long as the CU with
+// the most of them, w = ceil(i-blocks * slices / 256): w times a slice's
+// interactions and its start (about 64 interactions), and 0.8 slices more in
+// which its SIMDs have too few waves (measured at 65536 particles: w = 1 runs
+// at 0.56 of the rate of w = 20, w = 8 at 0.97).  The kick reads every slice's
+// sums.  The partial sums stay within kStaticScratchBytes where one slice's do.
+struct Slices {
+  uint32_t per, used;
+};
+
+Slices nb_slices(uint32_t n) {
   const uint32_t iblocks = (n + NB_T - 1) / NB_T;
-  uint32_t sl = 1;
-  while (iblocks * sl < 2048 && sl * NB_T * 2 <= n) sl *= 2;
-  return sl;
+  const uint64_t cap = std::max<uint64_t>(1, kStaticScratchBytes / (12ull * n));
+  Slices best{};
+  uint64_t cost = UINT64_MAX;
+  for (uint32_t w = 1; w <= 32; ++w) {
+    const uint64_t want = std::min<uint64_t>(cap, std::max<uint32_t>(1, 256u * w / iblocks));
+    const uint32_t per = (uint32_t)(((n + want - 1) / want + 63u) / 64u * 64u);
+    const uint32_t used = (n + per - 1) / per;
+    const uint64_t c = (5u * (((uint64_t)iblocks * used + 255u) / 256u) + 4u) * (per + 64u) + 8u * used;
+    if (c < cost) {
+      cost = c;
+      best = {per, used};
+    }
+  }
+  return best;
 }
 
 // Bytes of per-slice partial accelerations for n particles.
-size_t nb_scratch_bytes(uint32_t n) { return (size_t)nb_slices(n) * 3u * n * sizeof(float); }
+size_t nb_scratch_bytes(uint32_t n) { return n ? (size_t)nb_slices(n).used * 3u * n * sizeof(float) : 0; }
 
 // Largest particle count whose partial accelerations fit the static scratch
 // (for n >= 2^19 one slice, 12 bytes per particle).
@@ -564,17 +600,15 @@ constexpr uint32_t kNoallocMaxParticles = (uint32_t)(kStaticScratchBytes / 12u);
 // (nb_scratch_bytes(n) bytes; every element read is written first).
 llama_status nb_launch_steps(const Side& s, const NbCount& cnt, uint32_t n, uint32_t steps, float dt, float eps2,
                              float* part, hipStream_t st) {
-  const uint32_t slices = nb_slices(n);
-  uint32_t per = (n + slices - 1) / slices;
-  per = (per + NB_T - 1) / NB_T * NB_T;
-  const uint32_t iblocks = (n + NB_T - 1) / NB_T;
-  const uint32_t used = (n + per - 1) / per;
+  const Slices sl = nb_slices(n);
+  const uint32_t iblocks = (n + NB_T - 1) / NB_T, per = sl.per, used = sl.used;
+  const bool count = cnt.fac || cnt.heat[0];
+  const auto update = count ? k_nb_update<true> : k_nb_update<false>;
+  const auto move = s.layout == LY_STREAM ? (count ? k_nb_kick_drift_stream<true> : k_nb_kick_drift_stream<false>)
+                                          : (count ? k_nb_kick_drift<true> : k_nb_kick_drift<false>);
   for (uint32_t k = 0; k < steps; ++k) {
-    hipLaunchKernelGGL(k_nb_update, dim3(iblocks, used), dim3(NB_T), 0, st, s, n, eps2, per, part, cnt);
-    if (s.layout == LY_STREAM)
-      hipLaunchKernelGGL(k_nb_kick_drift_stream, dim3(iblocks), dim3(NB_T), 0, st, s, n, dt, used, part, cnt);
-    else
-      hipLaunchKernelGGL(k_nb_kick_drift, dim3(iblocks), dim3(NB_T), 0, st, s, n, dt, used, part, cnt);
+    hipLaunchKernelGGL(update, dim3(iblocks, used), dim3(NB_T), 0, st, s, n, eps2, per, part, cnt);
+    hipLaunchKernelGGL(move, dim3(iblocks), dim3(NB_T), 0, st, s, n, dt, used, part, cnt);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LLAMA_ERR_HIP, std::string("n-body launch: ") + hipGetErrorString(e));
