@@ -20,6 +20,7 @@ extent fastest).
 """
 import ctypes as C
 import os
+import sys
 
 __all__ = [
     "LlamaError", "lib", "View", "Batch", "LaunchParams", "BatchInfo",
@@ -174,8 +175,17 @@ def _extents(extents):
     return (C.c_uint64 * len(extents))(*extents), len(extents)
 
 
+def _raw_stream(torch):
+    return getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
+        # The handle of torch's current stream, read directly once torch runs on a
+        # GPU: 0.4 us a call, half of a small copy's host time through a Stream object.
+        torch = sys.modules.get("torch")
+        if torch is not None and _raw_stream(torch) is not None and torch.cuda.is_initialized():
+            return C.c_void_p(_raw_stream(torch)(torch._C._cuda_getDevice()))
         try:
             import torch
             if torch.cuda.is_available():
