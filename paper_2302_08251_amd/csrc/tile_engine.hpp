@@ -937,8 +937,46 @@ __device__ __forceinline__ void store_split_fused16(const Side& s, const Side& d
   }
 }
 
+// One 16-byte window of column c (columns of U bytes, `plane` bytes each) of a
+// line-owner tile: lane l holds the 16 bytes `own` of run q; the window starts
+// ph bytes before it (ph = the column's phase mod 16) and joins the left
+// neighbour's last ph bytes and the lane's first 16 - ph.  It is written as far
+// as it lies in the bytes that the tile owns in that column; only the ends of
+// a column cut a window.  Everything but q and `own` is wave-uniform, so the
+// store has one resource for the wave (with a base per line, each store ran
+// once per line: 1001 records of 7 x f32 into byte planes 19.5 us against 10.7,
+// 3 Mi from AoSoA 44.6 against 37.2, into element planes 40.4 against 36.2).
+template <int U>
+__device__ __forceinline__ void store_window(const Side& d, uint64_t plane, uint32_t c, uint64_t i0, uint32_t nt,
+                                             uint32_t q, bool writer, const u32x4& own) {
+  const uint64_t p0 = plane * c, pe = p0 + plane;
+  const uint64_t t0 = p0 + i0 * U, te = t0 + (uint64_t)nt * U;
+  const uint32_t ph = (uint32_t)t0 & 15u;
+  const uint64_t base = t0 - ph;  // window q starts at base + 16 q
+  const uint64_t b0 = i0 == 0 ? t0 : (t0 + 127u) & ~127ull;
+  uint64_t b1 = i0 + nt >= d.n ? pe : (te + 127u) & ~127ull;
+  if (b1 > pe) b1 = pe;
+  const uint32_t lo = (uint32_t)(b0 - base), hi = (uint32_t)(b1 - base);  // the owned bytes
+  const int src_lane = (int)((lane_id() ? lane_id() - 1u : 0u) * 4u);
+  const u32x4 prev = u32x4{(uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.x),
+                           (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.y),
+                           (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.z),
+                           (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.w)};
+  const u32x4 win = ph ? funnel16(prev, own, ph) : own;
+  const auto rs = make_rsrc((const uint8_t*)d.blob[0] + base, d.blob_size - base);
+  const uint32_t off = 16u * q;
+  if (!writer || off >= hi || off + 16u <= lo) return;
+  if (off >= lo && off + 16u <= hi) {
+    __builtin_amdgcn_raw_buffer_store_b128(win, rs, off, 0, kStoreNT);
+  } else {
+    const uint32_t w[4] = {win.x, win.y, win.z, win.w};
+    const uint32_t u0 = off < lo ? (lo - off) / U : 0u, u1 = off + 16u > hi ? (hi - off) / U : 16u / U;
+    store_chunk<U>(rs, off, w, ((1u << u1) - 1u) & ~((1u << u0) - 1u), 0x1FFFFu);
+  }
+}
+
 // The 16-byte split with line-owner writes (single-blob byte planes off the
-// line grid, see store_lines): the tile's source image holds its records and
+// line grid, see store_window): the tile's source image holds its records and
 // the halo (nl records), lanes take runs of 16 records of one field as in
 // store_split_fused16, and the 16-byte window that starts ph bytes before a
 // lane's run (ph = the plane's phase mod 16) is written when it lies inside
@@ -957,7 +995,6 @@ __device__ __forceinline__ void store_split_lines16(const Side& s, const Side& d
   const uint32_t w0 = wave_id(), nw = num_waves(), lane = lane_id();
   const Div dg = make_div_dev(gpf);
   const uint32_t items = F * gpf;
-  const bool first = i0 == 0, last = i0 + nt >= d.n;
   for (uint32_t it = w0; it < items; it += nw) {
     const uint32_t f = fdiv(it, dg);
     const int qi = (int)((it - f * gpf) * 63u + lane) - 1;
@@ -987,38 +1024,9 @@ __device__ __forceinline__ void store_split_lines16(const Side& s, const Side& d
       }
     }
 #pragma unroll
-    for (int k = 0; k < ES; ++k) {
-      const uint32_t c = f * ES + k;
-      const uint64_t p0 = d.n * c, pe = p0 + d.n;  // byte plane c in the blob
-      const uint64_t t0 = p0 + i0, te = t0 + nt;
-      const uint64_t b0 = first ? t0 : (t0 + 127u) & ~127ull;
-      uint64_t b1 = last ? pe : (te + 127u) & ~127ull;
-      if (b1 > pe) b1 = pe;
-      const uint32_t ph = (uint32_t)t0 & 15u;  // wave-uniform
-      const u32x4 own = has ? u32x4{col[k][0], col[k][1], col[k][2], col[k][3]} : u32x4{0u, 0u, 0u, 0u};
-      const int src_lane = (int)((lane ? lane - 1u : 0u) * 4u);
-      const u32x4 prev = u32x4{(uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.x),
-                               (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.y),
-                               (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.z),
-                               (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.w)};
-      if (!writer) continue;
-      const uint64_t ws = t0 + 16ull * q - ph;  // the window, 16-byte aligned
-      if (ws >= b1 || ws + 16u <= b0) continue;
-      const uint64_t base = ws & ~127ull;
-      const auto rs = make_rsrc((const uint8_t*)d.blob[0] + base, d.blob_size - base);
-      const uint32_t lo = (uint32_t)(ws - base);
-      if (ws >= b0 && ws + 16u <= b1) {
-        __builtin_amdgcn_raw_buffer_store_b128(ph ? funnel16(prev, own, ph) : own, rs, lo, 0, kStoreNT);
-      } else {
-        for (uint32_t j = 0; j < 16u; ++j) {
-          const uint64_t gb = ws + j;
-          if (gb < b0 || gb >= b1) continue;
-          const uint32_t b = j < ph ? 16u - ph + j : j - ph;  // byte of the neighbour's run, or of the own run
-          const u32x4& src = j < ph ? prev : own;
-          __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(src[b >> 2] >> (8u * (b & 3u))), rs, lo + j, 0, 0);
-        }
-      }
-    }
+    for (int k = 0; k < ES; ++k)
+      store_window<1>(d, d.n, f * ES + k, i0, nt, q, writer,
+                      has ? u32x4{col[k][0], col[k][1], col[k][2], col[k][3]} : u32x4{0u, 0u, 0u, 0u});
   }
 }
 
@@ -1082,7 +1090,7 @@ __device__ __forceinline__ u32x4 read_merge16(const Side& s, const uint8_t* lds,
   }
 }
 
-// Line-owner writes of destination columns of U bytes (see store_lines): a
+// Line-owner writes of destination columns of U bytes (see store_window): a
 // lane's run is 16 bytes of one column (16 / U records), given by read(r, c);
 // the 16-byte window starting ph bytes before it joins the left neighbour's
 // last ph bytes and the run's first 16 - ph bytes, and is written when it
@@ -1098,7 +1106,6 @@ __device__ __forceinline__ void store_lines16(const Side& d, uint64_t i0, uint32
   const uint32_t w0 = wave_id(), nw = num_waves(), lane = lane_id();
   const Div dg = make_div_dev(gpf);
   const uint32_t items = C * gpf;
-  const bool first = i0 == 0, last = i0 + nt >= d.n;
   const uint64_t plane = d.n * U;
   for (uint32_t it = w0; it < items; it += nw) {
     const uint32_t c = fdiv(it, dg);
@@ -1106,35 +1113,7 @@ __device__ __forceinline__ void store_lines16(const Side& d, uint64_t i0, uint32
     const bool has = qi >= 0 && qi < (int)runs;
     const uint32_t q = qi >= 0 ? (uint32_t)qi : 0u;
     const bool writer = lane != 0u && qi >= 0 && qi < (int)wins;
-    const u32x4 own = has ? read(q * R, c) : u32x4{0u, 0u, 0u, 0u};
-    const uint64_t p0 = plane * c, pe = p0 + plane;
-    const uint64_t t0 = p0 + i0 * U, te = t0 + (uint64_t)nt * U;
-    const uint64_t b0 = first ? t0 : (t0 + 127u) & ~127ull;
-    uint64_t b1 = last ? pe : (te + 127u) & ~127ull;
-    if (b1 > pe) b1 = pe;
-    const uint32_t ph = (uint32_t)t0 & 15u;  // wave-uniform
-    const int src_lane = (int)((lane ? lane - 1u : 0u) * 4u);
-    const u32x4 prev = u32x4{(uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.x),
-                             (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.y),
-                             (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.z),
-                             (uint32_t)__builtin_amdgcn_ds_bpermute(src_lane, (int)own.w)};
-    if (!writer) continue;
-    const uint64_t ws = t0 + 16ull * q - ph;
-    if (ws >= b1 || ws + 16u <= b0) continue;
-    const uint64_t base = ws & ~127ull;
-    const auto rs = make_rsrc((const uint8_t*)d.blob[0] + base, d.blob_size - base);
-    const uint32_t lo = (uint32_t)(ws - base);
-    if (ws >= b0 && ws + 16u <= b1) {
-      __builtin_amdgcn_raw_buffer_store_b128(ph ? funnel16(prev, own, ph) : own, rs, lo, 0, kStoreNT);
-    } else {
-      for (uint32_t j = 0; j < 16u; ++j) {
-        const uint64_t gb = ws + j;
-        if (gb < b0 || gb >= b1) continue;
-        const uint32_t b = j < ph ? 16u - ph + j : j - ph;
-        const u32x4& src = j < ph ? prev : own;
-        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(src[b >> 2] >> (8u * (b & 3u))), rs, lo + j, 0, 0);
-      }
-    }
+    store_window<U>(d, plane, c, i0, nt, q, writer, has ? read(q * R, c) : u32x4{0u, 0u, 0u, 0u});
   }
 }
 
@@ -1549,20 +1528,36 @@ __device__ __forceinline__ uint64_t convert(uint64_t v) {
   else return widen<8, 7, 11, 52>(v);
 }
 
+// Work items of the loops over fields below: `count` lane items of each field
+// (quads, chunks); a wave takes 64 of one field at a time, the fields' groups
+// in turn over the waves.  (With the whole workgroup on one field after
+// another, tiles of many fields, which hold few items of each, left most lanes
+// idle.)
+template <typename Body>
+__device__ __forceinline__ void for_groups(uint32_t F, uint32_t count, Body&& body) {
+  const uint32_t gpf = (count + 63u) >> 6;
+  const Div dg = make_div_dev(gpf);
+  const uint32_t items = F * gpf, nw = num_waves();
+  for (uint32_t it = wave_id(); it < items; it += nw) {
+    const uint32_t f = fdiv(it, dg);
+    const uint32_t q = (it - f * gpf) * 64u + lane_id();
+    if (q < count) body(f, q);
+  }
+}
+
 // Element planes on both sides, runs on the 16-byte grid: a lane converts the
 // 16 / ES_DST values of one destination chunk from contiguous source
 // elements (wide LDS reads) and stores the chunk whole.
 template <int CONV>
 __device__ __forceinline__ void store_conv_planar(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
-                                                  const uint8_t* lds, uint32_t f) {
+                                                  const uint8_t* lds) {
   constexpr int ESS = ConvInfo<CONV>::ES_SRC, ESD = ConvInfo<CONV>::ES_DST;
   constexpr int V = 16 / ESD;         // values per destination chunk
   constexpr int NB = V * ESS;         // source bytes per chunk: 4 .. 64
-  const uint32_t chunks = (nt + V - 1u) / V;
-  const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
-  const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start);
-  const uint8_t* plane = lds + f * s.lds_stride;
-  for (uint32_t c = threadIdx.x; c < chunks; c += blockDim.x) {
+  for_groups(d.ncols, (nt + V - 1u) / V, [&](uint32_t f, uint32_t c) {
+    const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
+    const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start);
+    const uint8_t* plane = lds + f * s.lds_stride;
     const uint32_t r = c * V;
     uint32_t raw[NB / 4];
     const uint8_t* p = plane + r * ESS;
@@ -1593,7 +1588,7 @@ __device__ __forceinline__ void store_conv_planar(const Side& s, const Side& d, 
     }
     const uint32_t valid = nt - r >= (uint32_t)V ? (1u << V) - 1u : (1u << (nt - r)) - 1u;
     store_chunk<ESD>(rs, 16u * c, w, valid, (1u << V) - 1u);
-  }
+  });
 }
 
 // Narrowing f32 -> f16 / bf16 on element planes: a lane converts the four
@@ -1603,15 +1598,14 @@ __device__ __forceinline__ void store_conv_planar(const Side& s, const Side& d, 
 // 16 KiB tiles f64 -> f32 measured 11 % slower.)
 template <int CONV>
 __device__ __forceinline__ void store_conv_planar_narrow(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
-                                                         const uint8_t* lds, uint32_t f) {
+                                                         const uint8_t* lds) {
   constexpr int ESS = ConvInfo<CONV>::ES_SRC, ESD = ConvInfo<CONV>::ES_DST;
   constexpr int V = 16 / ESS;      // values per source chunk (4 or 2)
   constexpr int OB = V * ESD;      // destination bytes per chunk (8 or 4)
-  const uint32_t chunks = (nt + V - 1u) / V;
-  const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
-  const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start);
-  const uint8_t* plane = lds + f * s.lds_stride;
-  for (uint32_t c = threadIdx.x; c < chunks; c += blockDim.x) {
+  for_groups(d.ncols, (nt + V - 1u) / V, [&](uint32_t f, uint32_t c) {
+    const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
+    const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start);
+    const uint8_t* plane = lds + f * s.lds_stride;
     const uint32_t r = c * V;
     const u32x4 x = *(const u32x4*)(plane + 16u * c);
     uint32_t w[2] = {0u, 0u};
@@ -1635,7 +1629,7 @@ __device__ __forceinline__ void store_conv_planar_narrow(const Side& s, const Si
           __builtin_amdgcn_raw_buffer_store_b32(w[bit >> 5], rs, off + ESD * k, 0, 0);
       }
     }
-  }
+  });
 }
 
 template <int CONV, int U, int DL, int SL>
@@ -1644,10 +1638,8 @@ __device__ __forceinline__ void store_conv(const Side& s, const Side& d, uint64_
   if constexpr (DL == LY_PLANAR && SL == LY_PLANAR && U == ConvInfo<CONV>::ES_DST) {
     constexpr uint32_t ESS = ConvInfo<CONV>::ES_SRC, ESD = ConvInfo<CONV>::ES_DST;
     if (s.cs == ESS && (s.mb || ((s.n * ESS) & 15u) == 0u) && (d.mb || ((d.n * ESD) & 15u) == 0u)) {
-      for (uint32_t f = 0; f < d.ncols; ++f) {
-        if constexpr (ESS == 4 && ESD == 2) store_conv_planar_narrow<CONV>(s, d, i0, nt, lds, f);
-        else store_conv_planar<CONV>(s, d, i0, nt, lds, f);
-      }
+      if constexpr (ESS == 4 && ESD == 2) store_conv_planar_narrow<CONV>(s, d, i0, nt, lds);
+      else store_conv_planar<CONV>(s, d, i0, nt, lds);
       return;
     }
   }
@@ -1769,22 +1761,6 @@ __device__ __forceinline__ void pack_quad_words(const uint32_t (&c)[4], uint32_t
   }
 }
 
-// Work items of the quad loops below: a wave takes 64 quads (four consecutive
-// records each) of one field at a time, the fields' groups in turn over the
-// waves.  (With the whole workgroup on one field after another, tiles of many
-// fields, which hold few quads of each, left most lanes idle.)
-template <typename Body>
-__device__ __forceinline__ void for_quads(uint32_t F, uint32_t nt, Body&& body) {
-  const uint32_t quads = (nt + 3u) >> 2, gpf = (quads + 63u) >> 6;
-  const Div dg = make_div_dev(gpf);
-  const uint32_t items = F * gpf, nw = num_waves();
-  for (uint32_t it = wave_id(); it < items; it += nw) {
-    const uint32_t f = fdiv(it, dg);
-    const uint32_t q = (it - f * gpf) * 64u + lane_id();
-    if (q < quads) body(f, q);
-  }
-}
-
 // Codes of four consecutive 4-byte values of field f straight from registers
 // to the stream (B = 8 * NWQ): the quad's codes are NWQ whole words, so a wave
 // writes 64 * NWQ * 4 contiguous bytes per store.  The tile's last, partial
@@ -1792,7 +1768,7 @@ __device__ __forceinline__ void for_quads(uint32_t F, uint32_t nt, Body&& body) 
 template <int NWQ, int CODEC, int FMT, int SL>
 __device__ __forceinline__ void pack_direct(const Side& s, const Side& d, uint64_t i0, uint32_t nt, uint32_t nw,
                                             const uint8_t* lds) {
-  for_quads(d.ncols, nt, [&](uint32_t f, uint32_t q) {
+  for_groups(d.ncols, (nt + 3u) >> 2, [&](uint32_t f, uint32_t q) {
     const uint64_t start = seg_start<LY_STREAM>(d, f, i0);
     const auto rs = make_rsrc((const uint8_t*)seg_blob<LY_STREAM>(d, f) + start, d.blob_size - start);
     uint32_t v[4], c[4], w[4];
@@ -1827,7 +1803,7 @@ template <int CLS, int CODEC, int FMT, int SL>
 __device__ __forceinline__ void pack_image(const Side& s, const Side& d, uint32_t nt, const uint8_t* lds,
                                            uint32_t* words, uint32_t wstride) {
   const uint32_t B = d.bits;
-  for_quads(d.ncols, nt, [&](uint32_t f, uint32_t q) {
+  for_groups(d.ncols, (nt + 3u) >> 2, [&](uint32_t f, uint32_t q) {
     uint32_t* wf = words + f * wstride;
     const uint32_t r = 4u * q;
     uint32_t v[4], c[4];
@@ -1921,7 +1897,7 @@ template <int CODEC, int DL>
 __device__ __forceinline__ void store_unpack_quads(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
                                                    const uint8_t* lds, uint8_t* img) {
   const uint32_t B = s.bits;
-  for_quads(d.ncols, nt, [&](uint32_t f, uint32_t q) {
+  for_groups(d.ncols, (nt + 3u) >> 2, [&](uint32_t f, uint32_t q) {
     const uint8_t* plane = lds + f * s.lds_stride;
     const uint32_t r = 4u * q;
     uint32_t v[4];
