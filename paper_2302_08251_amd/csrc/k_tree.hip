@@ -18,7 +18,7 @@
 //
 // The CU's one scalar unit bounds the small leaves: what a wave decodes per
 // leaf is kept short (the plan holds each leaf's addresses and steps ready, a
-// wave takes a leaf over hundreds of records, K = 4 records a lane share the
+// wave takes a leaf over hundreds of records, K = 8 records a lane share the
 // branches; with the branches taken per record the same copies were up to 2.4
 // times slower).  A store instruction that covers part of a line costs the
 // whole line's write unless the other parts reach L2 at once: hence the images,
@@ -27,8 +27,9 @@
 //
 // 5 Mi records {u8, f64, i16, f32} (150 MB moved a copy) in 27-37 us, padded
 // AoS destinations in 64 us; one thread per record and leaf took 77-114 us.
-// 3 Mi records of 3 integers between i32, i16 and 12-bit codes in 18-27 us, one
-// thread per 32 records took 130-237 us.
+// 3 Mi records of 3 integers between i32, i16 and 12-bit codes in 20-25 us, one
+// thread per 32 records took 130-237 us.  (K = 4: 8 Mi records of 7 leaves into
+// AoS 87 us, K = 8 70; the other copies within 5 %.)
 #include "value_codec.hpp"
 
 namespace lm {
@@ -58,7 +59,7 @@ __device__ __forceinline__ uint32_t place(const Place& p, uint32_t r) {
 }
 
 // The values of one leaf for K records a lane, 64 apart.
-constexpr uint32_t K = 4;
+constexpr uint32_t K = 8;
 constexpr uint32_t kStep = 64u * K;  // records per wave and pass
 
 // Element of B bytes at LDS address a, at any alignment.
