@@ -1261,7 +1261,11 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
       if ((a.leaf[l].dst & 3u) == TR_BITS) b += t * ((a.leaf[l].dst >> 4) & 127u) / 8u + 16u;
     return b;
   };
-  if (lds_bytes(gran) > kMaxTileLds || segs.size() > kMaxCols) return;
+  if (segs.size() > kMaxCols) return;
+  if (lds_bytes(gran) > kMaxTileLds) {  // long AoSoA blocks: without the record images
+    std::fill(rec_img, rec_img + kMaxGroups, 0u);
+    if (lds_bytes(gran) > kMaxTileLds) return;
+  }
   // 20 KiB a tile, 28 KiB where part of it is images (over 18 copies of 3 and
   // 5 Mi records: 12 KiB 776 us in all, 20 KiB 656, 32 KiB 661, 48 KiB 734; the
   // copies with images gain up to 18 % from 20 to 32 KiB, the others lose as

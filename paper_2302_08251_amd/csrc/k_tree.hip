@@ -23,7 +23,10 @@
 // times slower).  A store instruction that covers part of a line costs the
 // whole line's write unless the other parts reach L2 at once: hence the images,
 // and the waves working on the leaves of the same records together (padded
-// AoS records: 413 MB written for 120 MB of lines before, 121 MB now).
+// AoS records: 413 MB written for 120 MB of lines before, 121 MB now).  Such
+// records' lines leave with holes, which the memory fills by reading: they
+// bound the padded destinations (stored by full dwords and bytes from an image,
+// with half the requests, they took the same time).
 //
 // 5 Mi records {u8, f64, i16, f32} (150 MB moved a copy) in 27-37 us, padded
 // AoS destinations in 64 us; one thread per record and leaf took 77-114 us.

@@ -48,6 +48,7 @@ CASES = [
     (I3, MB, ct(["i16", "u8", "i32"], SB)), (I3, ct(["i16", "u32", "i8"], AOS), bpi(12)), (I3, bpi(9), bpi(16)),
     (I3, bpi(11), ct(["i64", "u16", "i32"], ao(40))), (I3[2:], AOS, bpi(41)), (I3[2:], bpi(63), SB),
     (F3, bpf(8, 15), bpf(5, 10)), (F3, bpf(5, 9), bpf(8, 12, round="rne")), (F3, ct(["f16", "f32", "f64"], SB), bpf(6, 13)),
+    (["u8", "i16", "f32", "u8", "f64", "u16"], MB, AOS), (["u16", "u8", "u16", "u8", "i32"], split(3, AOS, MB), split(4, AOS, SB)),
     (["f16", "bf16"], bpf(4, 7), ao(16)), (F3, bpf(8, 7), ct(["bf16", "f16", "f32"], AOS)),
 ]
 
