@@ -648,7 +648,14 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
     // see below.  Unpacks of several 4-byte fields: 12 KiB of stream words
     // (8 KiB 42.4 us into AoS, 12 KiB 37.5, 16 KiB with longer output tiles 39.7).
     const uint64_t target = pack_direct ? (D.bits == 8 || S.ncols > 1 ? 24576 : 16384) : pack ? 32768
-                            : line ? (D.cs == 1 && S.cs > 1 ? 32768 : 24576)  // the tile and its halo
+                            // line-owner tiles and their halo: byte planes as much as
+                            // 768 records need, whose windows nearly fill a wave's
+                            // step (7 x f64 between byte planes 407 us with 32 KiB,
+                            // 294 with 52); element planes from byte planes 32 KiB (24:
+                            // +7 %), from elements 16 KiB (30 Mi x 7 f32 300-319 us
+                            // against 326-333 with 24 KiB)
+                            : line ? (D.cs == 1 ? std::min<uint64_t>(std::max<uint64_t>(32768, lds_total(768)), 53248)
+                                                : S.cs == 1 ? 32768 : 16384)
                             : unpack ? (S.ncols > 1 && D.es == 4 ? 12288 : 8192)
                             // ChangeType: 32 KiB on the wider side; f32 -> f16 / bf16
                             // 16 KiB (measured on planes: 4096 values beat 8192 by 5-8 %)
