@@ -347,8 +347,8 @@ llama_status nbody_step(llama_view* particles, uint32_t steps, float dt, float e
  * bit), but no library allocation on any call: the per-slice partial
  * accelerations live in a static device array of 16 MiB that each GPU the
  * library runs on holds until the process ends.  That array fits at most
- * 1398101 particles (12 bytes of partial sums per particle once a view has
- * 2^19 particles or more); a larger view returns LLAMA_ERR_NO_MEMORY and
+ * 1398101 particles (12 bytes of partial sums per particle and slice of the
+ * j range, and as many slices as fit); a larger view returns LLAMA_ERR_NO_MEMORY and
  * nothing is enqueued.  Every call on one GPU shares that GPU's array and
  * writes every element it reads, so nothing needs clearing between calls;
  * calls that overlap in time on one GPU (other streams, other threads) race

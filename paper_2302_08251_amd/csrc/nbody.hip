@@ -593,7 +593,8 @@ Slices nb_slices(uint32_t n) {
 size_t nb_scratch_bytes(uint32_t n) { return n ? (size_t)nb_slices(n).used * 3u * n * sizeof(float) : 0; }
 
 // Largest particle count whose partial accelerations fit the static scratch
-// (for n >= 2^19 one slice, 12 bytes per particle).
+// (12 bytes per particle and slice; nb_slices keeps to one slice where two do
+// not fit).
 constexpr uint32_t kNoallocMaxParticles = (uint32_t)(kStaticScratchBytes / 12u);
 
 // The launches of `steps` update + move steps, partial sums in `part`
