@@ -1163,9 +1163,11 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
                       uint32_t grp, bool blocks) {
     return kind | lsz << 2 | bits << 4 | E << 11 | M << 15 | form << 21 | flag << 24 | grp << 25 | (blocks ? 1u << 28 : 0u);
   };
-  // bytes between two records of a leaf (inside a block: between two elements)
+  // bytes between two records of a leaf or byte column (inside a block of several
+  // records: between two elements); blocks of one record are records, also of bytes
   auto step = [](uint32_t kind, const MixGroup& g, uint32_t size) -> uint32_t {
-    return kind == TR_BYTES ? 1u : kind != TR_ELEM ? 0u : g.L == 1u ? (uint32_t)g.block : size;
+    if (kind != TR_ELEM && kind != TR_BYTES) return 0u;
+    return g.L == 1u ? (uint32_t)g.block : kind == TR_BYTES ? 1u : size;
   };
   uint64_t gran = 128;
   struct Seg { const uint8_t* base; uint64_t bits; uint32_t lanes, grp; bool group; };
