@@ -170,8 +170,9 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
   if (counting && blockIdx.y == 0)
     for (uint32_t f = 0; f < 3; ++f) nb_count(cnt, s, f, 0, i, i < n);
   uint32_t jloads = 0;  // j-tile loads of this thread (each of leaves 0, 1, 2, 6)
-  // running sums with compensation (Kahan) across j-tiles
-  float ax = 0.f, ay = 0.f, az = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
+  // running sums with compensation (Kahan) across j-tiles, and plain ones: the
+  // compensation of an infinite sum is a NaN, the plain sum stays infinite
+  float ax = 0.f, ay = 0.f, az = 0.f, cx = 0.f, cy = 0.f, cz = 0.f, sx = 0.f, sy = 0.f, sz = 0.f;
   for (uint32_t jt = j0; jt < j1; jt += NB_T) {
     const uint32_t j = jt + threadIdx.x;
     const uint16_t me = (uint16_t)threadIdx.x;  // this thread's particle in the j-tile
@@ -213,13 +214,14 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
     y = tx - cx; t = ax + y; cx = (t - ax) - y; ax = t;
     y = ty - cy; t = ay + y; cy = (t - ay) - y; ay = t;
     y = tz - cz; t = az + y; cz = (t - az) - y; az = t;
+    sx += tx; sy += ty; sz += tz;
     __syncthreads();
   }
   if (i < n) {
     float* p = part + (size_t)blockIdx.y * 3u * n;
-    p[i] = ax;
-    p[n + i] = ay;
-    p[2u * n + i] = az;
+    p[i] = __builtin_isfinite(ax) ? ax : sx;
+    p[n + i] = __builtin_isfinite(ay) ? ay : sy;
+    p[2u * n + i] = __builtin_isfinite(az) ? az : sz;
   }
   if (COUNT && cnt.fac) {
     nb_fac_add(cnt, 0, jloads);
@@ -230,21 +232,25 @@ __global__ __launch_bounds__(NB_T) void k_nb_update(const Side s, uint32_t n, fl
 }
 
 // Sum of the slices' accelerations in fixed order, compensated (Kahan): the
-// number of slices then does not show in the result.
+// number of slices then does not show in the result.  Sums that are not finite
+// are taken plainly, so that an infinity stays one.
 __device__ __forceinline__ void nb_accel(const float* __restrict__ part, uint32_t n, uint32_t slices, uint32_t i,
                                          float (&a)[3]) {
-  float c[3] = {0.f, 0.f, 0.f};
+  float c[3] = {0.f, 0.f, 0.f}, plain[3] = {0.f, 0.f, 0.f};
   a[0] = a[1] = a[2] = 0.f;
 #pragma unroll 8
   for (uint32_t sl = 0; sl < slices; ++sl) {
     const float* p = part + (size_t)sl * 3u * n;
 #pragma unroll
     for (uint32_t k = 0; k < 3; ++k) {
-      const float y = p[k * n + i] - c[k], t = a[k] + y;
+      const float x = p[k * n + i], y = x - c[k], t = a[k] + y;
       c[k] = (t - a[k]) - y;
       a[k] = t;
+      plain[k] += x;
     }
   }
+#pragma unroll
+  for (uint32_t k = 0; k < 3; ++k) a[k] = __builtin_isfinite(a[k]) ? a[k] : plain[k];
 }
 
 // Kick (v += dt a) then drift (x += dt v as stored), physical storage.
