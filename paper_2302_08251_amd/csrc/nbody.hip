@@ -374,7 +374,7 @@ __device__ __forceinline__ double rsqrt64(double x) {
 // sum over j in [j0, j1) of m_j (|x_i - x_j|^2 + eps2)^(-1/2), over j > i only
 // with DIAG.  The j rows are uniform: they come through scalar loads and the
 // arithmetic reads them as scalar operands.  FAST: every distance is finite
-// and eps2 > 0.
+// and 0 < eps2 < inf.
 template <bool DIAG, bool FAST>
 __device__ __forceinline__ double pair_sum(const double4* __restrict__ pm, uint32_t j0, uint32_t j1, uint32_t i,
                                            const double4& p, double eps2) {
@@ -422,8 +422,8 @@ __global__ __launch_bounds__(NB_T) void k_nb_potential(const double4* __restrict
     const uint32_t j1 = n - j0 < jc ? n : j0 + jc;
     const double4 p = pm[i < n ? i : n - 1u];
     // positions come from float32, so squared distances are finite unless a
-    // position is not; a run that holds such a particle takes the plain form
-    bool ok = eps2 > 0.0 && __builtin_isfinite(p.x + p.y + p.z);
+    // position or eps2 is not; such a run takes the plain form
+    bool ok = eps2 > 0.0 && __builtin_isfinite(eps2) && __builtin_isfinite(p.x + p.y + p.z);
     for (uint32_t j = j0 + threadIdx.x; j < j1; j += NB_T) {
       const double4 q = pm[j];
       ok = ok && __builtin_isfinite(q.x + q.y + q.z);
