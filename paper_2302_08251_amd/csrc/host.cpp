@@ -906,7 +906,7 @@ llama_status plan_xpose(const llama_view* src, const llama_view* dst, Plan& plan
   plan.kind = PK_XPOSE;
   plan.unit = U;
   plan.ntiles = a.ntiles;
-  plan.grid = (uint32_t)std::min<uint64_t>(a.ntiles, 1u << 24);
+  plan.grid = (uint32_t)std::min<uint64_t>(a.ntiles, kMaxGrid);
   a.xcd = plan.grid == a.ntiles ? 1u : 0u;
   plan.lds = (uint32_t)((lds_of() + 15u) & ~15ull);
   plan.alg_bytes = mapped_bytes(src->rec, src->map, src->n) + mapped_bytes(dst->rec, dst->map, dst->n);
@@ -1291,7 +1291,7 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
   while (k > 1 && (src->n + gran * k - 1) / (gran * k) < 512) k = (k + 1) / 2;
   const uint64_t tile = gran * k;
   const uint64_t ntiles = (src->n + tile - 1) / tile;
-  if (ntiles > 0x7FFFFFFFull) return;
+  if (ntiles > kMaxGrid) return;  // one workgroup a tile; the record-per-thread kernels loop
   uint64_t at = 0;
   uint32_t scol[kMaxCols] = {}, img[kMaxFields] = {};
   for (size_t q = 0; q < segs.size(); ++q) {

@@ -20,6 +20,7 @@ constexpr uint32_t kMaxFields = 64;
 constexpr uint32_t kMaxCols = 64;
 constexpr uint32_t kThreads = 256;            // threads per workgroup of the tile kernels
 constexpr uint32_t kMaxTileLds = 64 * 1024;   // LDS bytes per tile
+constexpr uint32_t kMaxGrid = (1u << 24) - 1;  // workgroups of kThreads in a launch, which takes fewer than 2^32 threads
 // Items (4 records x 1 field) per thread that the in-place merge of a
 // Bytesplit source into an AoS image holds in registers, by leaf bytes.
 template <int ES> constexpr int kMergeInPlaceItems = ES == 8 ? 4 : 8;
