@@ -873,25 +873,45 @@ llama_status plan_xpose(const llama_view* src, const llama_view* dst, Plan& plan
     ++a.nmid;
   }
   const uint32_t U = std::min(S.cs, D.cs);
-  // tiles of one column (the wider side's) unless a side is record-major
-  const bool whole = S.layout == LY_AOS || D.layout == LY_AOS;
+  // Tile edges: runs of 256 bytes in memory, along Q in the source and along P
+  // in the destination, where a column's run has 64 records of 4 or 8 bytes
+  // and a record-major one 32 (of at least two columns); no longer than the axis
+  // (a tile of 64 x 64 on an axis of 3 left most of its loads empty: 1000 x 1000
+  // x 3 records of 3 x u8, AoSoA to planes, 350 us, fitted 93)
+  auto edge = [&](const Side& x, uint64_t e) -> uint32_t {
+    uint32_t l = 0;
+    while (l < (x.layout == LY_AOS ? 5u : U >= 4u ? 6u : 7u) && (1ull << l) < e) ++l;
+    return l;
+  };
+  a.log2Q = edge(S, a.eQ);
+  a.log2P = edge(D, a.eP);
+  // tiles of one column (the wider side's) unless a side is record-major, or
+  // the tiles are so small (256 records) and many that the workgroups' starts
+  // count (2 x 400001 x 2 records of 3 x f32, AoSoA to planes: 3.6 ms by columns
+  // in tiles of 64 x 64, 0.30 in whole records, fitted edges and single waves)
+  const uint32_t area = a.log2P + a.log2Q;
+  const bool whole = S.layout == LY_AOS || D.layout == LY_AOS || (area <= 8u && src->n >> area >= 1024u);
   const uint32_t per = whole ? S.rec_bytes : std::max(S.cs, D.cs);  // bytes of a record in a tile
   a.nunits = per / U;
   a.nparts = S.rec_bytes / per;
   a.div_units = make_div(a.nunits);
-  // Tile edges: runs of 256 bytes in memory, along Q in the source and along P
-  // in the destination, where a column's run has 64 records of 4 or 8 bytes
-  // and a record-major one 32 (of at least two columns); less where the tile
-  // then takes over 27000 bytes of LDS (six workgroups a CU: over 11 copies
-  // 468 us in all, with 40960 478, with longer runs and 53000 545) or where
-  // there are too few tiles to fill the chip
-  auto edge = [&](const Side& x) -> uint32_t { return x.layout == LY_AOS ? 5u : U >= 4u ? 6u : 7u; };
-  a.log2Q = edge(S);
-  a.log2P = edge(D);
+  // smaller edges where the tile takes over 27000 bytes of LDS (six workgroups
+  // a CU: over 11 copies 468 us in all, with 40960 478, with longer runs and
+  // 53000 545), and where there are too few tiles to fill the chip: down to the
+  // 2048 units that a workgroup has in flight at once (1000 x 1000 f32 5.6 us,
+  // with 512 units 9.2), and below that for a few tiles only
   auto lds_of = [&] { return ((uint64_t)per << a.log2Q) * ((1u << a.log2P) + xpose_pad(U)); };
   auto shrink = [&] { --(a.log2P >= a.log2Q ? a.log2P : a.log2Q); };
+  auto units = [&] { return a.nunits << (a.log2P + a.log2Q); };
   while (lds_of() > 27000 && (a.log2P > 3 || a.log2Q > 3)) shrink();
-  while ((src->n * a.nparts) >> (a.log2P + a.log2Q) < 1024 && (a.log2P > 4 || a.log2Q > 4)) shrink();
+  for (;;) {
+    const uint64_t tiles = (src->n * a.nparts) >> (a.log2P + a.log2Q);
+    if ((a.log2P <= 4 && a.log2Q <= 4) || tiles >= 512 || (tiles >= 64 && units() <= 2048)) break;
+    shrink();
+  }
+  // one wave for a tile of one unit a thread or less: four times the workgroups
+  // fit a CU (2 x 400001 x 2 records of f32 259 us, with four waves 1010)
+  a.log2T = units() <= kThreads && a.log2P <= 6 && a.log2Q <= 6 ? 6 : 8;
   auto lmag = [](const Side& x) -> uint64_t {
     if (x.layout != LY_AOSOA || (x.lanes & (x.lanes - 1)) == 0) return 0;
     return ~0ull / x.lanes + 1ull;  // ceil(2^64 / L) for L not a power of two

@@ -127,13 +127,15 @@ struct TileArgs {
 // consecutive source records (along Q) for each of TP values along P.
 // Records move in units of U bytes (U = the smaller column size of the two
 // sides).  Where neither side keeps whole records together, a tile takes the
-// units of one column only.  Counts and strides are in records.
+// units of one column only, or of whole records where the axes are short.
+// Counts and strides are in records.
 struct XposeArgs {
   Side src;
   Side dst;
   uint32_t nunits;          // units per record in a tile
   uint32_t nparts;          // tiles that share a tile's records, each with its own units
   uint32_t log2P, log2Q;    // tile edges
+  uint32_t log2T;           // threads of a workgroup: 64 or 256
   uint32_t nmid;            // middle axes
   uint32_t xcd;             // 1: one workgroup per tile, each XCD a contiguous run of tiles
   Div div_units;

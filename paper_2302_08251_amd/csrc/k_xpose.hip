@@ -54,12 +54,13 @@ template <> struct Unit<8> { typedef uint64_t T; };
 
 // One side's walk over a tile: `rows` positions along one axis, each with a
 // run of `len` records consecutive in this side's memory.  `base` is the record
-// of (row 0, position 0), `stride` the records between rows.  body(row, pos,
-// unit, address) is called for every unit, K addresses of a lane at a time
-// through get(k, ...) and then put(k, ...), so that K accesses are in flight.
+// of (row 0, position 0), `stride` the records between rows.  Every unit is
+// visited twice: get(k, valid, address), for XK units of a lane one after
+// another, so that XK accesses are in flight, then put(k, valid, row, position,
+// unit) for the same ones.
 constexpr uint32_t XK = 8;
 
-template <int U, int L, typename Get, typename Put>
+template <int U, int L, uint32_t T, typename Get, typename Put>
 __device__ __forceinline__ void xp_walk(const Side& s, uint64_t lmag, uint32_t u0, uint32_t nu, const Div& dnu,
                                         uint64_t base, uint64_t stride, uint32_t rows, uint32_t len, uint32_t log2len,
                                         Get&& get, Put&& put) {
@@ -69,11 +70,11 @@ __device__ __forceinline__ void xp_walk(const Side& s, uint64_t lmag, uint32_t u
     const Div dr = make_div_dev(run);
     uint8_t* p0 = (uint8_t*)s.blob[0] + base * s.rec_bytes;
     const uint64_t rb = stride * s.rec_bytes;
-    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += XK * kThreads) {
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += XK * T) {
       uint32_t row[XK], x[XK];
 #pragma unroll
       for (uint32_t k = 0; k < XK; ++k) {
-        const uint32_t i = i0 + k * kThreads, j = i < total ? i : total - 1u;
+        const uint32_t i = i0 + k * T, j = i < total ? i : total - 1u;
         row[k] = fdiv(j, dr);
         x[k] = j - row[k] * run;
         get(k, i < total, p0 + row[k] * rb + x[k] * U);
@@ -81,14 +82,23 @@ __device__ __forceinline__ void xp_walk(const Side& s, uint64_t lmag, uint32_t u
 #pragma unroll
       for (uint32_t k = 0; k < XK; ++k) {
         const uint32_t r = fdiv(x[k], dnu);
-        put(k, i0 + k * kThreads < total, row[k], r, x[k] - r * nu);
+        put(k, i0 + k * T < total, row[k], r, x[k] - r * nu);
       }
     }
   } else {
     // per unit: lanes over the positions of a row; a lane keeps its position
     const uint32_t pos = threadIdx.x & ((1u << log2len) - 1u), row0 = threadIdx.x >> log2len;
-    const uint32_t step = kThreads >> log2len;  // rows between a lane's steps (tile edges are at most 128)
+    const uint32_t step = T >> log2len;  // rows between a lane's steps (tile edges are at most 128)
     const uint32_t at = pos < len ? pos : len - 1u;
+    if (rows <= step) {  // short axes: one row a lane
+      const bool ok = row0 < rows && pos < len;
+      const uint64_t i = base + (row0 < rows ? row0 : 0u) * stride + at;
+      for (uint32_t u = 0; u < nu; ++u) {
+        get(0, ok, xp_addr<U>(s, lmag, i, u0 + u));
+        put(0, ok, row0, pos, u);
+      }
+      return;
+    }
     for (uint32_t u = 0; u < nu; ++u) {
       uint8_t* p = nullptr;
       if constexpr (L == LY_PLANAR) p = xp_addr<U>(s, 0, base + row0 * stride + at, u0 + u);
@@ -112,8 +122,9 @@ __device__ __forceinline__ void xp_walk(const Side& s, uint64_t lmag, uint32_t u
   }
 }
 
-template <int U, int SL, int DL>
-__global__ __launch_bounds__(kThreads) void k_xpose(const XposeArgs a) {
+// T: threads of a workgroup, 64 (tiny tiles) or 256.
+template <int U, int SL, int DL, uint32_t T>
+__global__ __launch_bounds__(T) void k_xpose(const XposeArgs a) {
   typedef typename Unit<U>::T W;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   W* img = (W*)lds_raw;
@@ -123,32 +134,39 @@ __global__ __launch_bounds__(kThreads) void k_xpose(const XposeArgs a) {
     const uint64_t t = a.xcd ? xcd_tile((uint32_t)b, (uint32_t)a.ntiles) : b;
     // tile -> (units, middle index, tile along Q, tile along P): neighbours
     // along P share the lines at their runs' ends in the destination
-    uint64_t rest = t / a.nPt;
-    const uint64_t p0 = (t - rest * a.nPt) << lp;
-    uint64_t m = rest / a.nQt;
-    const uint64_t q0 = (rest - m * a.nQt) << lq;
-    uint64_t sbase = 0, dbase = 0;
-    for (uint32_t k = 0; k < a.nmid; ++k) {  // last middle axis varies fastest
-      const uint32_t j = a.nmid - 1u - k;
-      const uint64_t y = m / a.mext[j], x = m - y * a.mext[j];
-      m = y;
-      sbase += x * a.msrc[j];
-      dbase += x * a.mdst[j];
-    }
-    const uint32_t u0 = (uint32_t)m * nu;
+    uint64_t p0, q0, sbase = 0, dbase = 0;
+    uint32_t u0;
+    auto locate = [&](auto x) {
+      typedef decltype(x) I;
+      I rest = x / (I)a.nPt;
+      p0 = (uint64_t)(x - rest * (I)a.nPt) << lp;
+      I m = rest / (I)a.nQt;
+      q0 = (uint64_t)(rest - m * (I)a.nQt) << lq;
+      for (uint32_t k = 0; k < a.nmid; ++k) {  // last middle axis varies fastest
+        const uint32_t j = a.nmid - 1u - k;
+        rest = m / (I)a.mext[j];
+        const uint64_t y = m - rest * (I)a.mext[j];
+        m = rest;
+        sbase += y * a.msrc[j];
+        dbase += y * a.mdst[j];
+      }
+      u0 = (uint32_t)m * nu;
+    };
+    if (a.xcd) locate((uint32_t)t);  // fewer than 2^24 tiles
+    else locate(t);
     const uint32_t np = (uint32_t)(a.eP - p0 < (1u << lp) ? a.eP - p0 : (1u << lp));
     const uint32_t nq = (uint32_t)(a.eQ - q0 < (1u << lq) ? a.eQ - q0 : (1u << lq));
     sbase += p0 * a.sP + q0;  // source record of (p, q) = sbase + p sP + q
     dbase += q0 * a.dQ + p0;  // destination record of (p, q) = dbase + q dQ + p
     W v[XK];
-    xp_walk<U, SL>(a.src, a.src_lmag, u0, nu, a.div_units, sbase, a.sP, np, nq, lq,
+    xp_walk<U, SL, T>(a.src, a.src_lmag, u0, nu, a.div_units, sbase, a.sP, np, nq, lq,
                    [&](uint32_t k, bool ok, const uint8_t* p) { v[k] = ok ? *(const W*)p : (W)0; },
                    [&](uint32_t k, bool ok, uint32_t p, uint32_t q, uint32_t u) {
                      if (ok) img[((u << lq) + q) * row + p] = v[k];
                    });
     __syncthreads();
     uint8_t* to[XK];
-    xp_walk<U, DL>(a.dst, a.dst_lmag, u0, nu, a.div_units, dbase, a.dQ, nq, np, lp,
+    xp_walk<U, DL, T>(a.dst, a.dst_lmag, u0, nu, a.div_units, dbase, a.dQ, nq, np, lp,
                    [&](uint32_t k, bool ok, uint8_t* p) { to[k] = p; },
                    [&](uint32_t k, bool ok, uint32_t q, uint32_t p, uint32_t u) {
                      if (ok) *(W*)to[k] = img[((u << lq) + q) * row + p];
@@ -157,12 +175,18 @@ __global__ __launch_bounds__(kThreads) void k_xpose(const XposeArgs a) {
   }
 }
 
+template <int U, int SL, int DL>
+static void launch_t(const XposeArgs& a, uint32_t grid, uint32_t lds, hipStream_t st) {
+  if (a.log2T == 6u) hipLaunchKernelGGL((k_xpose<U, SL, DL, 64u>), dim3(grid), dim3(64), lds, st, a);
+  else hipLaunchKernelGGL((k_xpose<U, SL, DL, kThreads>), dim3(grid), dim3(kThreads), lds, st, a);
+}
+
 template <int U, int SL>
 static hipError_t launch_dl(const XposeArgs& a, uint32_t grid, uint32_t lds, hipStream_t st) {
   switch (a.dst.layout) {
-    case LY_AOS: hipLaunchKernelGGL((k_xpose<U, SL, LY_AOS>), dim3(grid), dim3(kThreads), lds, st, a); break;
-    case LY_PLANAR: hipLaunchKernelGGL((k_xpose<U, SL, LY_PLANAR>), dim3(grid), dim3(kThreads), lds, st, a); break;
-    default: hipLaunchKernelGGL((k_xpose<U, SL, LY_AOSOA>), dim3(grid), dim3(kThreads), lds, st, a); break;
+    case LY_AOS: launch_t<U, SL, LY_AOS>(a, grid, lds, st); break;
+    case LY_PLANAR: launch_t<U, SL, LY_PLANAR>(a, grid, lds, st); break;
+    default: launch_t<U, SL, LY_AOSOA>(a, grid, lds, st); break;
   }
   return hipGetLastError();
 }
