@@ -412,9 +412,8 @@ __global__ __launch_bounds__(kThreads) void k_tree(const TreeArgs a) {
       if (off < len) {
         if (off + 16u <= end) {
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(lds + (sg.lds & ~15u) + grp * 1024u), 16, off, 0, 0, kLoadStream);
-        } else {  // across the end: range checks work on whole dwords, so byte by byte
-          uint8_t* out = lds + (sg.lds & ~15u) + off;
-          for (uint32_t k = 0; k < 16u && off + k < end; ++k) out[k] = __builtin_amdgcn_raw_buffer_load_b8(rs, off + k, 0, 0);
+        } else {  // across the end
+          load_tail16(rs, off, lds + (sg.lds & ~15u) + off);
         }
       }
     }
