@@ -472,8 +472,7 @@ static bool plan_pack_planar(const llama_view* src, const llama_view* dst, Plan&
     if (x != t) return false;
   const uint32_t B = code_bits(dm);
   if (B % 8 == 0 || B > 27) return false;
-  PlanarPackArgs& a = plan.pp;
-  a = PlanarPackArgs{};
+  PlanarPackArgs a{};  // `plan` already holds the sides, for the tile kernels
   const uint64_t n = src->n;
   for (uint32_t f = 0; f < F; ++f) {
     const uint8_t* b0 = (const uint8_t*)src->blobs[0];
@@ -494,6 +493,7 @@ static bool plan_pack_planar(const llama_view* src, const llama_view* dst, Plan&
   a.n = n;
   a.nf = F;
   a.bits = B;
+  plan.pp = a;
   plan.kind = PK_PACK_PLANAR;
   plan.unit = 4;
   // one wave per chunk of 2048 values, one workgroup per four chunks
@@ -1140,11 +1140,12 @@ llama_status plan_generic(const llama_view* src, const llama_view* dst, Plan& pl
 
 // ---------------------------------------------------------------- tiled per-leaf copies
 
-// The rule of the tiled form: one linearisation order, AoSoA blocks that fit a
-// tile of at most 4096 records and 64 KiB.  It beats the record-per-thread
+// The rule of the tiled form: one linearisation order, AoSoA blocks of which a
+// multiple of 128 records fits a tile of 4096 records and 64 KiB (blocks of 100
+// records need 3200, blocks of 33 do not fit).  It beats the record-per-thread
 // kernels at every size measured (5 Mi records of {u8, f64, i16, f32}, AoS to
-// columns: 77 -> 34 us; 3 Mi records of 3 i32 into i16: 190 -> 22 us), so they
-// only keep the pairs outside it.
+// columns: 77 -> 34 us; 3 Mi records of 3 i32 into i16: 190 -> 22 us), so
+// they only keep the pairs outside it.
 
 // Bytes from `p` to the end of the view's blob that holds it.
 static uint64_t bytes_left(const llama_view* v, const uint8_t* p) {
@@ -1164,17 +1165,17 @@ static uint32_t tree_form(uint8_t t) {
   }
 }
 
-void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
-  if (orders_differ(src, dst) || src->n == 0) return;
+bool plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
+  if (orders_differ(src, dst) || src->n == 0) return false;
   static thread_local GenSide S, D;
   std::memset(&S, 0, sizeof(S));
   std::memset(&D, 0, sizeof(D));
-  uint32_t ng = 0, ncol = 0;
-  if (gen_flatten(src->rec, src->map, src->n, src->blobs.data(), 0, S, ng, ncol) != LLAMA_OK) return;
-  ng = ncol = 0;
-  if (gen_flatten(dst->rec, dst->map, dst->n, dst->blobs.data(), 0, D, ng, ncol) != LLAMA_OK) return;
-  auto args = std::make_shared<TreeArgs>();
-  TreeArgs& a = *args;
+  uint32_t ng = 0, scols = 0, dcols = 0;
+  if (gen_flatten(src->rec, src->map, src->n, src->blobs.data(), 0, S, ng, scols) != LLAMA_OK) return false;
+  ng = 0;
+  if (gen_flatten(dst->rec, dst->map, dst->n, dst->blobs.data(), 0, D, ng, dcols) != LLAMA_OK) return false;
+  plan = Plan{};
+  TreeArgs& a = plan.ta;
   const Rec& rec = src->rec;
   const uint32_t nf = (uint32_t)rec.size();
   uint32_t ops = 0;
@@ -1190,9 +1191,11 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
     return g.L == 1u ? (uint32_t)g.block : kind == TR_BYTES ? 1u : size;
   };
   uint64_t gran = 128;
-  struct Seg { const uint8_t* base; uint64_t bits; uint32_t lanes, grp; bool group; };
-  std::vector<Seg> segs;
-  std::vector<int> col_seg(kMaxCols, -1);
+  struct Seg { const uint8_t* base; uint64_t bits; uint32_t lanes; bool group; };
+  Seg segs[kMaxCols];  // one per source column at most
+  uint32_t nseg = 0;
+  uint8_t col_seg[kMaxCols];
+  std::fill(col_seg, col_seg + scols, (uint8_t)255);
   int grp_seg[kMaxGroups];
   const uint8_t* grp_base[kMaxGroups] = {};
   bool grp_used[2][kMaxGroups] = {};
@@ -1237,8 +1240,8 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
     // source segments: one per AoS or AoSoA part, one per plane, byte column or stream
     const uint32_t c0 = S.m.cidx[f];
     if (skind == TR_BITS) {
-      col_seg[c0] = (int)segs.size();
-      segs.push_back({S.m.col[c0], sb, 1, 0, false});
+      col_seg[c0] = (uint8_t)nseg;
+      segs[nseg++] = {S.m.col[c0], sb, 1, false};
     } else if (skind != TR_ZERO) {
       const MixGroup& g = S.m.g[sg];
       grp_used[0][sg] = true;
@@ -1246,14 +1249,14 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
       if (g.L) {
         if (g.L > 1u) gran = lcm64(gran, g.L);
         if (grp_seg[sg] < 0) {
-          grp_seg[sg] = (int)segs.size();
-          segs.push_back({grp_base[sg], 8ull * (g.block / g.L), g.L, sg, true});
+          grp_seg[sg] = (int)nseg;
+          segs[nseg++] = {grp_base[sg], 8ull * (g.block / g.L), g.L, true};
         }
-        for (uint32_t k = 0; k < cols; ++k) col_seg[c0 + k] = grp_seg[sg];
+        for (uint32_t k = 0; k < cols; ++k) col_seg[c0 + k] = (uint8_t)grp_seg[sg];
       } else {
         for (uint32_t k = 0; k < cols; ++k) {
-          col_seg[c0 + k] = (int)segs.size();
-          segs.push_back({S.m.col[c0 + k], skind == TR_BYTES ? 8u : 8u * ssz, 1, sg, false});
+          col_seg[c0 + k] = (uint8_t)nseg;
+          segs[nseg++] = {S.m.col[c0 + k], skind == TR_BYTES ? 8u : 8u * ssz, 1, false};
         }
       }
     }
@@ -1263,13 +1266,8 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
     }
     const uint32_t dcols = dkind == TR_BYTES ? dsz : 1u;
     for (uint32_t k = 0; k < dcols; ++k) a.dcol[D.m.cidx[f] + k] = const_cast<uint8_t*>(D.m.col[D.m.cidx[f] + k]);
-    if (gran > 4096) return;
+    if (gran > 4096) return false;
   }
-  // LDS of a tile of t records: every segment with its phase and 16 bytes of
-  // slack (misaligned reads fetch whole dwords), the bit-packed leaves' words
-  auto slot = [&](const Seg& s, uint64_t t) {
-    return (((uintptr_t)s.base & 15u) + t * s.bits / 8u + 15u) / 16u * 16u + 16u;
-  };
   // an AoS part whose records have no padding is put together in LDS and
   // stored whole; one of a single leaf is a plane
   uint32_t rec_img[kMaxGroups] = {}, dleaves[kMaxGroups] = {}, dfirst[kMaxGroups] = {};
@@ -1285,56 +1283,62 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
     const MixGroup& m = D.m.g[g];
     if (grp_used[1][g] && m.kind == MX_ELEM && m.L == 1u && m.block == dsum[g] && dleaves[g] > 1u) rec_img[g] = (uint32_t)m.block;
   }
-  auto lds_bytes = [&](uint64_t t) {
-    uint64_t b = 16;
-    for (const Seg& s : segs) b += slot(s, t);
-    for (uint32_t g = 0; g < kMaxGroups; ++g) b += (t * rec_img[g] + 15u) / 16u * 16u;
-    for (uint32_t l = 0; l < a.nleaf; ++l)
-      if ((a.leaf[l].dst & 3u) == TR_BITS) b += t * ((a.leaf[l].dst >> 4) & 127u) / 8u + 16u;
-    return b;
-  };
-  if (segs.size() > kMaxCols) return;
-  if (lds_bytes(gran) > kMaxTileLds) {  // long AoSoA blocks: without the record images
-    std::fill(rec_img, rec_img + kMaxGroups, 0u);
-    if (lds_bytes(gran) > kMaxTileLds) return;
+  // LDS of a tile of t records (t a multiple of 128), fixed + t * per_rec / 8:
+  // every segment with its phase and 16 bytes of slack (misaligned reads fetch
+  // whole dwords), the bit-packed leaves' words, the record images
+  uint64_t fixed = 16, per_rec = 0, images_rec = 0;
+  for (uint32_t q = 0; q < nseg; ++q) {
+    fixed += ((uintptr_t)segs[q].base & 15u) ? 32 : 16;
+    per_rec += segs[q].bits;
   }
+  bool images = false;
+  for (uint32_t l = 0; l < a.nleaf; ++l)
+    if ((a.leaf[l].dst & 3u) == TR_BITS) {
+      fixed += 16;
+      per_rec += (a.leaf[l].dst >> 4) & 127u;
+      images = true;
+    }
+  for (uint32_t g = 0; g < kMaxGroups; ++g) images_rec += 8u * rec_img[g];
+  if (fixed + gran / 8u * (per_rec + images_rec) > kMaxTileLds) {  // long AoSoA blocks: without the record images
+    std::fill(rec_img, rec_img + kMaxGroups, 0u);
+    images_rec = 0;
+    if (fixed + gran / 8u * per_rec > kMaxTileLds) return false;
+  }
+  images = images || images_rec != 0;
   // 20 KiB a tile, 28 KiB where part of it is images (over 18 copies of 3 and
   // 5 Mi records: 12 KiB 776 us in all, 20 KiB 656, 32 KiB 661, 48 KiB 734; the
   // copies with images gain up to 18 % from 20 to 32 KiB, the others lose as
   // much); smaller ones where that leaves the chip idle
-  bool images = false;
-  for (uint32_t g = 0; g < kMaxGroups; ++g) images = images || rec_img[g];
-  for (uint32_t l = 0; l < a.nleaf; ++l) images = images || (a.leaf[l].dst & 3u) == TR_BITS;
-  const uint64_t room = images ? 28672 : 20480;
-  uint64_t k = 1;
-  while (gran * (k + 1) <= 4096 && lds_bytes(gran * (k + 1)) <= room) ++k;
+  const uint64_t room = (images ? 28672 : 20480) - fixed, unit = gran / 8u * (per_rec + images_rec);
+  uint64_t k = std::max<uint64_t>(1, std::min<uint64_t>(4096 / gran, unit ? room / unit : 4096));
   while (k > 1 && (src->n + gran * k - 1) / (gran * k) < 512) k = (k + 1) / 2;
   const uint64_t tile = gran * k;
   const uint64_t ntiles = (src->n + tile - 1) / tile;
-  if (ntiles > kMaxGrid) return;  // one workgroup a tile; the record-per-thread kernels loop
+  if (ntiles > kMaxGrid) return false;  // one workgroup a tile; the record-per-thread kernels loop
   uint64_t at = 0;
   uint32_t scol[kMaxCols] = {}, img[kMaxFields] = {};
-  for (size_t q = 0; q < segs.size(); ++q) {
+  uint32_t seg_at[kMaxCols];
+  for (uint32_t q = 0; q < nseg; ++q) {
     const Seg& s = segs[q];
     const uint32_t ph = (uint32_t)((uintptr_t)s.base & 15u);
     TreeSeg& o = a.seg[q];
     o.base = s.base - ph;
-    o.lds = (uint32_t)at | ph;
+    o.lds = seg_at[q] = (uint32_t)at | ph;
     const uint64_t nr = (src->n + s.lanes - 1) / s.lanes * s.lanes;
     const uint64_t total = s.bits % 8u ? (nr * s.bits + 7u) / 8u : nr * (s.bits / 8u);
     const uint64_t after = std::min<uint64_t>(bytes_left(src, s.base) - total, 16u);
     o.what = (uint32_t)s.bits | s.lanes << 13 | (uint32_t)after << 26;
-    for (uint32_t c = 0; c < kMaxCols; ++c)
-      if (col_seg[c] == (int)q) scol[c] = (uint32_t)(at + ph + (s.group ? (uint64_t)(S.m.col[c] - s.base) : 0u));
-    at += slot(s, tile);
+    at += tile * s.bits / 8u + (ph ? 32u : 16u);
   }
-  a.nseg = (uint32_t)segs.size();
+  for (uint32_t c = 0; c < scols; ++c)
+    if (col_seg[c] != 255u) scol[c] = seg_at[col_seg[c]] + (segs[col_seg[c]].group ? (uint32_t)(S.m.col[c] - segs[col_seg[c]].base) : 0u);
+  a.nseg = nseg;
   at = std::max<uint64_t>(at, 16);  // image addresses are never 0
   a.img = (uint32_t)at;
   for (uint32_t l = 0; l < a.nleaf; ++l)
     if ((a.leaf[l].dst & 3u) == TR_BITS) {
       img[l] = (uint32_t)at;
-      at += (tile * ((a.leaf[l].dst >> 4) & 127u) / 8u + 16u + 15u) / 16u * 16u;
+      at += tile * ((a.leaf[l].dst >> 4) & 127u) / 8u + 16u;
     }
   a.img_bytes = (uint32_t)at - a.img;
   a.images = a.img_bytes ? 1u : 0u;
@@ -1347,7 +1351,7 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
       const uint32_t w = a.leaf[l].dst, c = (a.leaf[l].what >> 8) & 255u;
       if ((w & 3u) == TR_ELEM && (w >> 25 & 7u) == g) img[l] = (uint32_t)(at + (D.m.col[c] - D.m.col[c0]));
     }
-    at += (tile * rec_img[g] + 15u) / 16u * 16u;
+    at += tile * rec_img[g];
   }
   for (uint32_t g = 0; g < kMaxGroups; ++g)
     for (int side = 0; side < 2; ++side) {
@@ -1359,16 +1363,17 @@ void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
       o.tstride = m.L ? (uint32_t)(tile / m.L * m.block) : 0u;
       o.div_L = make_div(m.L);
     }
-  for (uint32_t c = 0; c < kMaxCols; ++c) a.scol[c >> 1] |= scol[c] << (16u * (c & 1u));
+  for (uint32_t c = 0; c < scols; ++c) a.scol[c >> 1] |= scol[c] << (16u * (c & 1u));
   for (uint32_t l = 0; l < a.nleaf; ++l) a.leaf[l].lds = scol[a.leaf[l].what & 255u] | img[l] << 16;
   a.n = src->n;
   a.tile = (uint32_t)tile;
-  plan.ta = std::move(args);
   plan.kind = PK_TREE;
   plan.unit = ops;
   plan.ntiles = a.nleaf ? ntiles : 0;
   plan.grid = (uint32_t)ntiles;
   plan.lds = (uint32_t)at;
+  plan.alg_bytes = mapped_bytes(src->rec, src->map, src->n) + mapped_bytes(dst->rec, dst->map, dst->n);
+  return true;
 }
 
 llama_status launch_plan(const Plan& plan, hipStream_t st) {
@@ -1383,7 +1388,7 @@ llama_status launch_plan(const Plan& plan, hipStream_t st) {
     case PK_XPOSE: e = launch_xpose(plan.xa, plan.unit, plan.grid, plan.lds, st); break;
     case PK_MIXED: e = launch_mixed(plan.ma, plan.grid, st); break;
     case PK_GENERIC: e = launch_generic(plan.ga, plan.grid, st); break;
-    case PK_TREE: e = launch_tree(*plan.ta, plan.unit, plan.grid, plan.lds, st); break;
+    case PK_TREE: e = launch_tree(plan.ta, plan.unit, plan.grid, plan.lds, st); break;
     case PK_PACK_PLANAR: e = launch_pack_planar(plan.pp, plan.grid, st); break;
   }
   if (e != hipSuccess) return fail(LLAMA_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
@@ -1719,29 +1724,40 @@ static llama_status plan_views(const llama_view* src, const llama_view* dst, con
     // any other partner: one per-leaf copy over both mapping trees (value by
     // value where a part is computed), then the counters of their
     // instrumented parts
-    CopyStep step;
-    llama_status s = plan_mixed(src, dst, step.plan);
-    if (s == LLAMA_ERR_UNSUPPORTED) s = plan_generic_or_keep(src, dst, step.plan);
-    if (s != LLAMA_OK) return s;
-    plan_tree(src, dst, step.plan);
-    steps.push_back(step);
+    steps.emplace_back();
+    Plan& plan = steps.back().plan;
+    if (!plan_tree(src, dst, plan)) {
+      llama_status s = plan_mixed(src, dst, plan);
+      if (s == LLAMA_ERR_UNSUPPORTED) s = plan_generic_or_keep(src, dst, plan);
+      if (s != LLAMA_OK) return s;
+    }
     count_parts(src, false, steps);
     count_parts(dst, true, steps);
     return LLAMA_OK;
   }
   if (dst->map.kind == LLAMA_MAP_NULL) return LLAMA_OK;
-  CopyStep step;
-  llama_status s;
-  if (mixed_record(dst->rec)) s = plan_mixed(src, dst, step.plan);  // leaves of several sizes
-  else if (src->map.kind == LLAMA_MAP_NULL) s = plan_zero(dst, step.plan);  // zeros in any order
-  else if (orders_differ(src, dst)) s = plan_xpose(src, dst, step.plan);
-  else s = plan_copy(src, dst, params, step.plan);
+  steps.emplace_back();
+  Plan& plan = steps.back().plan;
+  llama_status s = LLAMA_OK;
+  if (mixed_record(dst->rec)) {  // leaves of several sizes
+    if (plan_tree(src, dst, plan)) return LLAMA_OK;
+    s = plan_mixed(src, dst, plan);
+  } else if (src->map.kind == LLAMA_MAP_NULL) {
+    s = plan_zero(dst, plan);  // zeros in any order
+  } else if (orders_differ(src, dst)) {
+    s = plan_xpose(src, dst, plan);
+  } else {
+    s = plan_copy(src, dst, params, plan);
+  }
+  if (s != LLAMA_ERR_UNSUPPORTED) return s;
   // what the tile kernels do not move (two computed views, integer
   // ChangeType, codes over 32 bits, ...) is copied value by value
-  if (s == LLAMA_ERR_UNSUPPORTED) s = plan_generic_or_keep(src, dst, step.plan);
-  if (s != LLAMA_OK) return s;
-  if (step.plan.kind == PK_MIXED || step.plan.kind == PK_GENERIC) plan_tree(src, dst, step.plan);
-  steps.push_back(step);
+  const std::string why = g_error;
+  if (!plan_tree(src, dst, plan)) {
+    g_error = why;
+    return plan_generic_or_keep(src, dst, plan);
+  }
+  clear_error();
   return LLAMA_OK;
 }
 

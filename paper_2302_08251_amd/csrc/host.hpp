@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <memory>
 #include <string>
 #include <vector>
@@ -64,13 +65,19 @@ struct Plan {
   uint32_t lds = 0;
   uint64_t alg_bytes = 0;  // mapped bytes read + mapped bytes written
   uint64_t ntiles = 0;
-  TileArgs args{};
-  XposeArgs xa{};  // PK_XPOSE
-  MixArgs ma{};    // PK_MIXED
-  GenArgs ga{};    // PK_GENERIC
-  PlanarPackArgs pp{};  // PK_PACK_PLANAR
-  std::shared_ptr<TreeArgs> ta;  // PK_TREE
+  // the kernel arguments, by kind; at most 4 KiB, cleared and copied on every call
+  union {
+    TileArgs args;      // PK_RAW .. PK_ZERO
+    XposeArgs xa;       // PK_XPOSE
+    MixArgs ma;         // PK_MIXED
+    GenArgs ga;         // PK_GENERIC
+    PlanarPackArgs pp;  // PK_PACK_PLANAR
+    TreeArgs ta;        // PK_TREE
+    uint8_t bytes[4096];
+  };
+  Plan() { std::memset(bytes, 0, sizeof(bytes)); }
 };
+static_assert(sizeof(Plan) <= 4096 + 48, "every kernel's arguments fit `bytes`");
 
 // Builds the device description of a view.  UNSUPPORTED when the tile
 // engine does not cover the mapping.
@@ -111,9 +118,11 @@ llama_status plan_mixed(const llama_view* src, const llama_view* dst, Plan& plan
 // ChangeType, bit-packed codes up to 64 bits, bit-packed f16 / bf16).
 llama_status plan_generic(const llama_view* src, const llama_view* dst, Plan& plan);
 
-// The tiled form of a per-leaf or value-level copy: replaces `plan` when both
-// sides share one order and their AoSoA blocks fit a tile.
-void plan_tree(const llama_view* src, const llama_view* dst, Plan& plan);
+// The tiled form of a per-leaf or value-level copy.  False, with `plan` left in
+// no defined state, where it does not take the pair: sides in different orders,
+// AoSoA blocks that do not fit a tile, mappings that the per-leaf and
+// value-level copies do not take either.
+bool plan_tree(const llama_view* src, const llama_view* dst, Plan& plan);
 
 // Geometry of one blob of a physical layout for Heatmap counting: records
 // come in periods of `period` bytes holding `recs` records each (AoS: one
