@@ -1144,8 +1144,8 @@ llama_status plan_generic(const llama_view* src, const llama_view* dst, Plan& pl
 // multiple of 128 records fits a tile of 4096 records and 64 KiB (blocks of 100
 // records need 3200, blocks of 33 do not fit).  It beats the record-per-thread
 // kernels at every size measured (5 Mi records of {u8, f64, i16, f32}, AoS to
-// columns: 77 -> 34 us; 3 Mi records of 3 i32 into i16: 190 -> 22 us), so
-// they only keep the pairs outside it.
+// columns: 77 -> 34 us; 3 Mi records of 3 i32 into i16: 190 -> 22 us), unless
+// such long tiles are few: they only keep those and the pairs outside it.
 
 // Bytes from `p` to the end of the view's blob that holds it.
 static uint64_t bytes_left(const llama_view* v, const uint8_t* p) {
@@ -1315,6 +1315,10 @@ bool plan_tree(const llama_view* src, const llama_view* dst, Plan& plan) {
   const uint64_t tile = gran * k;
   const uint64_t ntiles = (src->n + tile - 1) / tile;
   if (ntiles > kMaxGrid) return false;  // one workgroup a tile; the record-per-thread kernels loop
+  // few tiles of more than 1024 records: a record a thread fills more of the chip
+  // ({f32, f64} from AoSoA-31 to byte planes, tiles of 3968: 200000 records 8 us
+  // against 13, 500000 10 against 13, 1 Mi 15 against 14)
+  if (gran >= 1024 && ntiles < 256 && src->n > 512) return false;
   uint64_t at = 0;
   uint32_t scol[kMaxCols] = {}, img[kMaxFields] = {};
   uint32_t seg_at[kMaxCols];
