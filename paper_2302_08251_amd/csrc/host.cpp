@@ -652,10 +652,11 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
                             // 768 records need, whose windows nearly fill a wave's
                             // step (7 x f64 between byte planes 407 us with 32 KiB,
                             // 294 with 52); element planes from byte planes 32 KiB (24:
-                            // +7 %), from elements 16 KiB (30 Mi x 7 f32 300-319 us
-                            // against 326-333 with 24 KiB)
+                            // +7 %; but with fewer than 256 such tiles 24: 30011 x 3
+                            // f64 12 us, with 32 KiB 13), from elements 16 KiB (30 Mi x 7
+                            // f32 300-319 us against 326-333 with 24 KiB)
                             : line ? (D.cs == 1 ? std::min<uint64_t>(std::max<uint64_t>(32768, lds_total(768)), 53248)
-                                                : S.cs == 1 ? 32768 : 16384)
+                                                : S.cs == 1 ? (S.n * S.rec_bytes >= 8u << 20 ? 32768 : 24576) : 16384)
                             : unpack ? (S.ncols > 1 && D.es == 4 ? 12288 : 8192)
                             // ChangeType: 32 KiB on the wider side; f32 -> f16 / bf16
                             // 16 KiB (measured on planes: 4096 values beat 8192 by 5-8 %)
