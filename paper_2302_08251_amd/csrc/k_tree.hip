@@ -413,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void k_tree(const TreeArgs a) {
         if (off + 16u <= end) {
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(lds + (sg.lds & ~15u) + grp * 1024u), 16, off, 0, 0, kLoadStream);
         } else {  // across the end
-          load_tail16(rs, off, lds + (sg.lds & ~15u) + off);
+          load_tail16(rs, off, end - off, lds + (sg.lds & ~15u) + off);
         }
       }
     }

@@ -138,18 +138,21 @@ __device__ __forceinline__ Div make_div_dev(uint32_t d) {
 // Phase A: source tile -> LDS, verbatim
 // ---------------------------------------------------------------------------
 
-// The 16 bytes at `off` of a buffer that ends inside them, zeros past its end.
-// Range checks work on whole dwords, so a size that is not a multiple of 4
-// would zero the last bytes: byte by byte, all loads in flight at once (a loop
-// over the bytes that are left waited for each: 10008 records of 3 x f64 from
-// one blob per byte plane, 24 tails, 17 us).
-__device__ __forceinline__ void load_tail16(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint8_t* to) {
-  uint32_t b[16];
-#pragma unroll
-  for (uint32_t k = 0; k < 16; ++k) b[k] = __builtin_amdgcn_raw_buffer_load_b8(rs, off + k, 0, 0);
+// The 16 bytes at `off` of a buffer that ends `left` bytes further (1..15), zeros
+// past its end.  Range checks work on whole dwords: the last, partial one comes
+// byte by byte.  All loads are in flight at once (a loop over the bytes waited for
+// each: 10008 records of 3 x f64 from one blob per byte plane, 24 tails, 17 us, now 12).
+__device__ __forceinline__ void load_tail16(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t left, uint8_t* to) {
   u32x4 v;
 #pragma unroll
-  for (uint32_t k = 0; k < 4; ++k) v[k] = b[4 * k] | (b[4 * k + 1] << 8) | (b[4 * k + 2] << 16) | (b[4 * k + 3] << 24);
+  for (uint32_t k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4u * k, 0, 0);
+  const uint32_t part = left & ~3u;
+  uint32_t w = 0u;
+#pragma unroll
+  for (uint32_t k = 0; k < 3; ++k)
+    w |= (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rs, off + part + k, 0, 0) << (8u * k);
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) v[k] = part == 4u * k ? w : v[k];
   *(u32x4*)to = v;
 }
 
@@ -163,7 +166,11 @@ __device__ __forceinline__ void load_tail16(__amdgpu_buffer_rsrc_t rs, uint32_t 
 // data read once; measured faster for copies (+2.5 % over the 36 layout
 // pairs) and packs (+10-20 %), slower for unpacks of narrow codes (-10-20 %)
 // and f64 sources of a conversion, which keep the default policy.
-template <int LT = -1, int FORM = 0, bool STREAM = true>
+//
+// TAILS: chunks across a blob's end by load_tail16, for the sides that may have
+// many (byte planes); in packs, conversions and unpacks, with one a field at
+// most, its code costs more (64 Mi f64 into 24 bits 164 us, with it 174).
+template <int LT = -1, int FORM = 0, bool STREAM = true, bool TAILS = true>
 __device__ __forceinline__ void load_tile(const Side& s, uint64_t i0, uint32_t nt, uint8_t* lds) {
   constexpr int L = FORM ? -1 : LT;
   const SegGeo g = seg_geo<L>(s, nt);
@@ -194,7 +201,14 @@ __device__ __forceinline__ void load_tile(const Side& s, uint64_t i0, uint32_t n
         else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, to, 16, chunk * 16u, 0, 0, 0);
       } else {
         // The chunk crosses the end of the blob.
-        load_tail16(rs, chunk * 16u, lds + seg_lds<L>(s, seg) + chunk * 16u);
+        uint8_t* out = lds + seg_lds<L>(s, seg) + chunk * 16u;
+        const uint64_t left = s.blob_size - (abase + chunk * 16ull);
+        if constexpr (TAILS) {
+          load_tail16(rs, chunk * 16u, (uint32_t)left, out);
+        } else {
+          for (uint32_t k = 0; k < 16u && k < left; ++k)
+            out[k] = __builtin_amdgcn_raw_buffer_load_b8(rs, chunk * 16u + k, 0, 0);
+        }
       }
     }
   }
