@@ -1553,45 +1553,54 @@ __device__ __forceinline__ uint64_t convert(uint64_t v) {
 }
 
 // Loop over `count` lane items (quads) of each field: a wave takes 64 of one
-// field at a time, the fields' groups in turn over the waves.  (With the whole
-// workgroup on one field after another, tiles of many fields, which hold few
-// items of each, left most lanes idle.)
-template <typename Body>
-__device__ __forceinline__ void for_groups(uint32_t F, uint32_t count, Body&& body) {
+// field at a time, the fields' groups in turn over the waves; at(f) gives what a
+// field's items share (its resource), anew only where the wave's field changes.
+// (With the whole workgroup on one field after another, tiles of many fields,
+// which hold few items of each, left most lanes idle.)
+template <typename At, typename Body>
+__device__ __forceinline__ void for_groups(uint32_t F, uint32_t count, At&& at, Body&& body) {
   const uint32_t gpf = (count + 63u) >> 6;
   const Div dg = make_div_dev(gpf);
   const uint32_t items = F * gpf, nw = num_waves();
+  uint32_t cur = 0;
+  auto c = at(0u);
   for (uint32_t it = wave_id(); it < items; it += nw) {
     const uint32_t f = fdiv(it, dg);
+    if (f != cur) {
+      cur = f;
+      c = at(f);
+    }
     const uint32_t q = (it - f * gpf) * 64u + lane_id();
-    if (q < count) body(f, q);
+    if (q < count) body(f, c, q);
   }
 }
 
 // The same for loops with little work per item: `full` whole items and with
-// `tail` a partial one, at(f) gives what a field's items share (its resource),
-// item(f, at, q, whole) does one.  Fields with enough items for all waves are
-// taken one after another by the whole workgroup, unrolled (one field of 1024
-// quads in groups of 64 set up its resource for each: 5.65 TB/s against 6.15 at
-// 16 bits; the unpacks and the word image, with more work per item, are up to
-// 20 % faster in groups).
-template <typename At, typename Item>
+// `tail` a partial one, item(f, at, q, whole) does one.  Fields with enough items
+// for all waves are taken one after another by the whole workgroup, unrolled (one
+// field of 1024 quads in groups of 64: 5.65 TB/s against 6.15 at 16 bits; the
+// unpacks and the word image, with more work per item, are up to 20 % faster in
+// groups).  APART: the partial item after the whole ones, which then need no
+// checks (an item with long arithmetic is done twice by its wave: 1001 f64
+// into f16 7.1 us, with the check 6.1).
+template <bool APART, typename At, typename Item>
 __device__ __forceinline__ void for_fields(uint32_t F, uint32_t full, bool tail, At&& at, Item&& item) {
-  const uint32_t nw = num_waves();
+  const uint32_t nw = num_waves(), count = full + (tail ? 1u : 0u);
   if (full >= 64u * nw) {
     for (uint32_t f = 0; f < F; ++f) {
       const auto c = at(f);
+      if constexpr (APART) {
 #pragma unroll 2
-      for (uint32_t q = threadIdx.x; q < full; q += blockDim.x) item(f, c, q, std::true_type{});
-      if (tail && threadIdx.x == 0) item(f, c, full, std::false_type{});
+        for (uint32_t q = threadIdx.x; q < full; q += blockDim.x) item(f, c, q, std::true_type{});
+        if (tail && threadIdx.x == 0) item(f, c, full, std::false_type{});
+      } else {
+#pragma unroll 2
+        for (uint32_t q = threadIdx.x; q < count; q += blockDim.x) item(f, c, q, q < full);
+      }
     }
     return;
   }
-  for_groups(F, full + (tail ? 1u : 0u), [&](uint32_t f, uint32_t q) {
-    const auto c = at(f);
-    if (q < full) item(f, c, q, std::true_type{});
-    else item(f, c, q, std::false_type{});
-  });
+  for_groups(F, count, at, [&](uint32_t f, const auto& c, uint32_t q) { item(f, c, q, q < full); });
 }
 
 // A field's resource from the tile's first byte of it, and its LDS plane.
@@ -1613,7 +1622,7 @@ __device__ __forceinline__ void store_conv_planar(const Side& s, const Side& d, 
     const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
     return FieldRun{make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start), lds + f * s.lds_stride};
   };
-  for_fields(d.ncols, nt / V, nt % V != 0u, at, [&](uint32_t, const FieldRun& fr, uint32_t c, auto whole) {
+  for_fields<false>(d.ncols, nt / V, nt % V != 0u, at, [&](uint32_t, const FieldRun& fr, uint32_t c, auto whole) {
     const uint32_t r = c * V;
     uint32_t raw[NB / 4];
     const uint8_t* p = fr.plane + r * ESS;
@@ -1662,7 +1671,7 @@ __device__ __forceinline__ void store_conv_planar_narrow(const Side& s, const Si
     const uint64_t start = seg_start<LY_PLANAR>(d, f, i0);
     return FieldRun{make_rsrc((const uint8_t*)seg_blob<LY_PLANAR>(d, f) + start, d.blob_size - start), lds + f * s.lds_stride};
   };
-  for_fields(d.ncols, nt / V, nt % V != 0u, at, [&](uint32_t, const FieldRun& fr, uint32_t c, auto whole) {
+  for_fields<false>(d.ncols, nt / V, nt % V != 0u, at, [&](uint32_t, const FieldRun& fr, uint32_t c, auto whole) {
     const uint32_t r = c * V;
     const auto rs = fr.rs;
     const u32x4 x = *(const u32x4*)(fr.plane + 16u * c);
@@ -1819,6 +1828,35 @@ __device__ __forceinline__ void pack_quad_words(const uint32_t (&c)[4], uint32_t
   }
 }
 
+// A field's 4-byte values in LDS, four consecutive ones at a time: `wide` where
+// every quad is 16 aligned bytes (planes on the 16-byte grid, AoSoA blocks of a
+// multiple of four records), one value for the wave (with the alignment looked at
+// per lane, one plane of 64 Mi f32 into 20-bit codes took 106 us against 101).
+struct QuadRun {
+  const uint8_t* base;  // the field's first value
+  bool wide;
+};
+
+template <int SL>
+__device__ __forceinline__ QuadRun quad_run(const Side& s, const uint8_t* lds, uint32_t f) {
+  const bool wide = SL == LY_PLANAR ? (planar_phase(s, f) & 15u) == 0u : SL == LY_AOSOA && (s.lanes & 3u) == 0u;
+  return QuadRun{lds + src_addr<SL>(s, 0, f * 4u), wide};
+}
+
+template <int SL>
+__device__ __forceinline__ void read_quad(const Side& s, const uint8_t* lds, const QuadRun& run, uint32_t q,
+                                          uint32_t f, uint32_t (&v)[4]) {
+  auto at = [&](uint32_t r) { return SL == LY_PLANAR ? run.base + 4u * r : lds + src_addr<SL>(s, r, f * 4u); };
+  if (run.wide) {
+    const u32x4 x = *(const u32x4*)at(4u * q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = x[k];
+  } else {
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) v[k] = *(const uint32_t*)at(4u * q + k);
+  }
+}
+
 // Codes of four consecutive 4-byte values of field f straight from registers
 // to the stream (B = 8 * NWQ): the quad's codes are NWQ whole words, so a wave
 // writes 64 * NWQ * 4 contiguous bytes per store.  The tile's last, partial
@@ -1826,13 +1864,18 @@ __device__ __forceinline__ void pack_quad_words(const uint32_t (&c)[4], uint32_t
 template <int NWQ, int CODEC, int FMT, int SL>
 __device__ __forceinline__ void pack_direct(const Side& s, const Side& d, uint64_t i0, uint32_t nt, uint32_t nw,
                                             const uint8_t* lds) {
+  struct Run {
+    __amdgpu_buffer_rsrc_t rs;
+    QuadRun quads;
+  };
   auto at = [&](uint32_t f) {
     const uint64_t start = seg_start<LY_STREAM>(d, f, i0);
-    return make_rsrc((const uint8_t*)seg_blob<LY_STREAM>(d, f) + start, d.blob_size - start);
+    return Run{make_rsrc((const uint8_t*)seg_blob<LY_STREAM>(d, f) + start, d.blob_size - start), quad_run<SL>(s, lds, f)};
   };
-  for_fields(d.ncols, nt >> 2, (nt & 3u) != 0u, at, [&](uint32_t f, __amdgpu_buffer_rsrc_t rs, uint32_t q, auto whole) {
+  for_fields<true>(d.ncols, nt >> 2, (nt & 3u) != 0u, at, [&](uint32_t f, const Run& run, uint32_t q, auto whole) {
+    const auto rs = run.rs;
     uint32_t v[4], c[4], w[4];
-    read_elems4<4, SL>(s, lds, 4u * q, f, v);
+    read_quad<SL>(s, lds, run.quads, q, f, v);
 #pragma unroll
     for (int k = 0; k < 4; ++k) c[k] = encode_fmt<CODEC, FMT>(v[k], d);
     const uint32_t off = 4u * NWQ * q;  // the quad's first word
@@ -1863,11 +1906,16 @@ template <int CLS, int CODEC, int FMT, int SL>
 __device__ __forceinline__ void pack_image(const Side& s, const Side& d, uint32_t nt, const uint8_t* lds,
                                            uint32_t* words, uint32_t wstride) {
   const uint32_t B = d.bits;
-  for_groups(d.ncols, (nt + 3u) >> 2, [&](uint32_t f, uint32_t q) {
-    uint32_t* wf = words + f * wstride;
+  struct Run {
+    QuadRun quads;
+    uint32_t* words;
+  };
+  auto at = [&](uint32_t f) { return Run{quad_run<SL>(s, lds, f), words + f * wstride}; };
+  for_groups(d.ncols, (nt + 3u) >> 2, at, [&](uint32_t f, const Run& run, uint32_t q) {
+    uint32_t* wf = run.words;
     const uint32_t r = 4u * q;
     uint32_t v[4], c[4];
-    read_elems4<4, SL>(s, lds, r, f, v);
+    read_quad<SL>(s, lds, run.quads, q, f, v);
 #pragma unroll
     for (int k = 0; k < 4; ++k) c[k] = encode_fmt<CODEC, FMT>(v[k], d);
     if (r + 4u > nt) {
@@ -1893,9 +1941,10 @@ __device__ __forceinline__ void store_pack(const Side& s, const Side& d, uint64_
   const uint32_t B = d.bits;
   const uint32_t F = d.ncols;
   const uint32_t nw = (nt * B + 31u) >> 5;  // stream words of this tile
+  // columns of 4-byte values (not Bytesplit byte columns): four values at a time
+  const bool quads = s.cs == 4u;
   if constexpr (ES == 4) {
-    // columns of 4-byte values (not Bytesplit byte columns): four values at a time
-    if (s.cs == 4u) {
+    if (quads) {
       if ((B & 7u) == 0u) {  // whole words, no image (the plan allots none)
         constexpr uint32_t FB = 1u + PackFmtInfo<FMT>::E + PackFmtInfo<FMT>::M;  // a fixed format's code bits
         if constexpr (FMT != PF_RUNTIME && FB % 8u == 0u) {
@@ -1916,7 +1965,7 @@ __device__ __forceinline__ void store_pack(const Side& s, const Side& d, uint64_
       else pack_image<3, CODEC, FMT, SL>(s, d, nt, lds, words, wstride);
     }
   }
-  if (ES != 4 || s.cs != 4u) {
+  if (ES != 4 || !quads) {
     for (uint32_t f = 0; f < F; ++f)
       for (uint32_t r = threadIdx.x; r < nt; r += blockDim.x)
         or_bits(words + f * wstride, r * B, encode_fmt<CODEC, FMT>(fetch_elem<ES, SL>(s, lds, r, f), d), B);
@@ -1957,8 +2006,19 @@ template <int CODEC, int DL>
 __device__ __forceinline__ void store_unpack_quads(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
                                                    const uint8_t* lds, uint8_t* img) {
   const uint32_t B = s.bits;
-  for_groups(d.ncols, (nt + 3u) >> 2, [&](uint32_t f, uint32_t q) {
-    const uint8_t* plane = lds + f * s.lds_stride;
+  auto at = [&](uint32_t f) {
+    if constexpr (DL == LY_AOS) {
+      return (const uint8_t*)(lds + f * s.lds_stride);
+    } else {
+      const void* blob = (DL == LY_PLANAR && d.mb) ? d.blob[f] : d.blob[0];
+      const uint64_t base = col_base<DL>(d, i0, f);
+      return FieldRun{make_rsrc((const uint8_t*)blob + base, d.blob_size - base), lds + f * s.lds_stride};
+    }
+  };
+  for_groups(d.ncols, (nt + 3u) >> 2, at, [&](uint32_t f, const auto& run, uint32_t q) {
+    const uint8_t* plane;
+    if constexpr (DL == LY_AOS) plane = run;
+    else plane = run.plane;
     const uint32_t r = 4u * q;
     uint32_t v[4];
 #pragma unroll
@@ -1968,9 +2028,7 @@ __device__ __forceinline__ void store_unpack_quads(const Side& s, const Side& d,
 #pragma unroll
       for (int k = 0; k < 4; ++k) *(uint32_t*)(to + k * d.rec_bytes) = v[k];
     } else {
-      const void* blob = (DL == LY_PLANAR && d.mb) ? d.blob[f] : d.blob[0];
-      const uint64_t base = col_base<DL>(d, i0, f);
-      const auto rs = make_rsrc((const uint8_t*)blob + base, d.blob_size - base);
+      const auto rs = run.rs;
       const uint32_t off = col_local<DL>(d, r);
       if (r + 4u <= nt) {
         __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0], v[1], v[2], v[3]}, rs, off, 0, kStoreNT);
