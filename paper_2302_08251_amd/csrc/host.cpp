@@ -479,7 +479,7 @@ static bool plan_pack_planar(const llama_view* src, const llama_view* dst, Plan&
     switch (sm.kind) {
       case LLAMA_MAP_SOA_MB: a.src[f] = (const uint8_t*)src->blobs[f]; break;
       case LLAMA_MAP_SOA_SB:
-        if (n % 4u) return false;  // planes on the 16-byte grid
+        if (F > 1 && n % 4u) return false;  // planes on the 16-byte grid
         a.src[f] = b0 + 4u * n * f;
         break;
       case LLAMA_MAP_AOS: case LLAMA_MAP_AOSOA:
@@ -530,6 +530,10 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
     plan.kind = PK_UNPACK;
     plan.unit = D.cs;
     plan.args.codec = codec_of(su);
+    if (D.ncols == 1 && D.layout != LY_PLANAR) {  // records of one column are a plane in every layout
+      D.layout = LY_PLANAR;
+      D.mb = 1;
+    }
   } else if (S.vkind == VK_RAW && D.vkind == VK_RAW) {
     plan.kind = PK_RAW;
     plan.unit = S.es;  // leaf bytes
@@ -601,13 +605,25 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
   // 4-byte values, B a multiple of 8)
   const bool pack = plan.kind == PK_PACK;
   const bool pack_direct = pack && S.cs == 4 && S.es == 4 && (D.bits & 7u) == 0;
-  // unpack into AoS records of 4-byte leaves: an LDS image of the tile's
-  // records, where it fits (explicit tiles may leave no room: gathered then)
-  const bool unpack_aos = plan.kind == PK_UNPACK && D.layout == LY_AOS && D.cs == 4 && D.es == 4;
+  // unpack of 4-byte leaves by quads of records.  AoS: through an LDS image of
+  // the tile's records, where it fits (explicit tiles may leave no room), unless
+  // the fields are a multiple of four, whose quads meet in few banks, or the tile
+  // has fewer than 256 records, whose quads do not fill a wave (7 fields 37.5 us,
+  // gathered 44; 6 fields 35 and 39; 8 fields 2.1, 4 fields 1.3, 24 fields 1.8
+  // times the time of the gather), or wider records make few tiles (15 fields
+  // 1.8 Mi records 0.9, 4097 records 1.1 times).  AoSoA blocks of
+  // a multiple of four records: the same tiles.
+  const bool unpack4 = plan.kind == PK_UNPACK && D.cs == 4 && D.es == 4;
+  const bool many = S.n * F * 4u >= 16u << 20;  // tiles of 16 KiB that fill the chip
+  const bool unpack_aos = unpack4 && D.layout == LY_AOS && D.ncols % 4u != 0 && D.rec_bytes * 256u <= 16384u &&
+                          (D.ncols <= 8 || many);
   auto unpack_lds = [&](uint64_t t) {
     return ((tile_lds_bytes(S, (uint32_t)t) + 15u) & ~15ull) + t * (uint64_t)D.rec_bytes;
   };
   auto unpack_image = [&](uint64_t t) { return unpack_aos && unpack_lds(t) <= kMaxTileLds; };
+  auto unpack_quads = [&](uint64_t t) {
+    return unpack4 && (D.layout == LY_PLANAR || unpack_image(t) || (D.layout == LY_AOSOA && D.lanes % 4u == 0 && t >= 256u));
+  };
   auto lds_total = [&](uint64_t t) -> uint64_t {
     // line-owner copies build the destination's runs in registers from the
     // tile's source image (and halo), the only LDS image (+16: a misaligned
@@ -645,9 +661,13 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
     // 20 % at B = 8) and for several fields, whose quads then fill the waves
     // (4 Mi records of 7 fields, 24 bits: from planes 37.2 us with 16 KiB, 36.3
     // with 24, 37.1 with 32).  Word-image packs: about 32 KiB with the image,
-    // see below.  Unpacks of several 4-byte fields: 12 KiB of stream words
-    // (8 KiB 42.4 us into AoS, 12 KiB 37.5, 16 KiB with longer output tiles 39.7).
-    const uint64_t target = pack_direct ? (D.bits == 8 || S.ncols > 1 ? 24576 : 16384) : pack ? 32768
+    // see below.  Unpacks of several 4-byte fields by quads: 12 KiB of stream
+    // words (7 fields, 8 KiB 42.4 us into AoS, 12 KiB 37.5, 16 KiB with longer
+    // output tiles 39.7; planes of up to 4 fields 8 KiB: 2 x 24 bits 34 us, with 12
+    // KiB 37).  Both longer tiles only where there are enough to fill the chip
+    // (4097 records of 4 fields into 24 bits 6.9 us with 24 KiB, 6.2 with 16).
+    const bool quads = unpack4 && (D.layout == LY_PLANAR || unpack_aos || (D.layout == LY_AOSOA && D.lanes % 4u == 0));
+    const uint64_t target = pack_direct ? (D.bits == 8 || (S.ncols > 1 && many) ? 24576 : 16384) : pack ? 32768
                             // line-owner tiles and their halo: byte planes as much as
                             // 768 records need, whose windows nearly fill a wave's
                             // step (7 x f64 between byte planes 407 us with 32 KiB,
@@ -657,7 +677,7 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
                             // f32 300-319 us against 326-333 with 24 KiB)
                             : line ? (D.cs == 1 ? std::min<uint64_t>(std::max<uint64_t>(32768, lds_total(768)), 53248)
                                                 : S.cs == 1 ? (S.n * S.rec_bytes >= 8u << 20 ? 32768 : 24576) : 16384)
-                            : unpack ? (S.ncols > 1 && D.es == 4 ? 12288 : 8192)
+                            : unpack ? (quads && many && S.ncols > (D.layout == LY_PLANAR ? 4u : 1u) ? 12288 : 8192)
                             // ChangeType: 32 KiB on the wider side; f32 -> f16 / bf16
                             // 16 KiB (measured on planes: 4096 values beat 8192 by 5-8 %)
                             : plan.kind == PK_CONV ? (S.es == 4 && D.es == 2 ? 16384 : 32768)
@@ -779,6 +799,7 @@ llama_status plan_copy(const llama_view* src, const llama_view* dst, const llama
       plan.args.can_off = (uint32_t)((tile_lds_bytes(S, (uint32_t)tile) + 15u) & ~15u);
     }
   }
+  if (plan.kind == PK_UNPACK) plan.args.colrun = unpack_quads(tile) ? 1u : 0u;
   // can_off 0: no word image (every field stored directly), no record image
   if ((pack && !pack_direct) || unpack_image(tile)) plan.args.can_off = (uint32_t)((tile_lds_bytes(S, (uint32_t)tile) + 15u) & ~15u);
   plan.args.tile = (uint32_t)tile;

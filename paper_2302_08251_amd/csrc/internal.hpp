@@ -114,7 +114,7 @@ struct TileArgs {
   uint32_t conv;        // Conv
   uint32_t codec;       // Codec (pack / unpack)
   uint32_t mode;        // RawMode
-  uint32_t colrun;      // 1: destination chunks are runs of one column (copied 16 bytes at a time)
+  uint32_t colrun;      // 1: destination chunks are runs of one column (copied 16 bytes at a time); unpack: by quads
   uint32_t can_off;     // LDS offset of the canonical image (MERGE / SPLIT / LINE)
   uint32_t halo;        // LINE: records loaded past the tile (128 / destination column bytes)
   Geo can;              // canonical image geometry (MERGE / SPLIT / LINE)

@@ -190,11 +190,11 @@ __device__ __forceinline__ void phase_b_pack(const Side& s, const Side& d, uint6
 
 template <int CODEC, int U>
 __device__ __forceinline__ void phase_b_unpack(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
-                                               const uint8_t* lds, uint8_t* img) {
+                                               const uint8_t* lds, bool quads, uint8_t* img) {
   switch (d.layout) {
-    case LY_AOS: store_unpack<CODEC, U, LY_AOS>(s, d, i0, nt, lds, img); break;
-    case LY_PLANAR: store_unpack<CODEC, U, LY_PLANAR>(s, d, i0, nt, lds, img); break;
-    default: store_unpack<CODEC, U, LY_AOSOA>(s, d, i0, nt, lds, img); break;
+    case LY_AOS: store_unpack<CODEC, U, LY_AOS>(s, d, i0, nt, lds, quads, img); break;
+    case LY_PLANAR: store_unpack<CODEC, U, LY_PLANAR>(s, d, i0, nt, lds, quads, img); break;
+    default: store_unpack<CODEC, U, LY_AOSOA>(s, d, i0, nt, lds, quads, img); break;
   }
 }
 
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kThreads) void k_tile(const TileArgs a) {
     wait_tile_loads();
     if constexpr (KIND == 1) phase_b_conv<P0, U>(a.src, a.dst, i0, nt, lds);
     else if constexpr (KIND == 2) phase_b_pack<P0, U>(a.src, a.dst, i0, nt, lds, words, wstride);
-    else phase_b_unpack<P0, U>(a.src, a.dst, i0, nt, lds, a.can_off ? lds + a.can_off : nullptr);
+    else phase_b_unpack<P0, U>(a.src, a.dst, i0, nt, lds, a.colrun != 0u, lds + a.can_off);
     __syncthreads();
   }
 }

@@ -1941,8 +1941,10 @@ __device__ __forceinline__ void store_pack(const Side& s, const Side& d, uint64_
   const uint32_t B = d.bits;
   const uint32_t F = d.ncols;
   const uint32_t nw = (nt * B + 31u) >> 5;  // stream words of this tile
-  // columns of 4-byte values (not Bytesplit byte columns): four values at a time
-  const bool quads = s.cs == 4u;
+  // columns of 4-byte values (not Bytesplit byte columns): four values at a time;
+  // but for the word image not from records of a multiple of 32 bytes, whose
+  // quads all lie in the same banks (8 x i32 into 29 bits 17 % slower than value by value)
+  const bool quads = s.cs == 4u && !(SL == LY_AOS && (s.rec_bytes & 31u) == 0u && (B & 7u) != 0u);
   if constexpr (ES == 4) {
     if (quads) {
       if ((B & 7u) == 0u) {  // whole words, no image (the plan allots none)
@@ -1997,8 +1999,9 @@ __device__ __forceinline__ void store_pack(const Side& s, const Side& d, uint64_
 // Unpack of 4-byte values, four consecutive records of a field per lane,
 // decoded straight from the stream words.  Planes and AoSoA blocks of a
 // multiple of four records: the quad is one 16-byte store (a wave writes whole
-// lines; planes may start at any element).  AoS: the quads are put into an LDS
-// image of the tile's records, which then leaves in 16-byte stores.  4 Mi
+// lines; planes may start at any element).  AoS records (see the plan for which):
+// the quads are put into an LDS image of the tile's records, which then leaves in
+// 16-byte stores.  4 Mi
 // records of 7 x f32 from 24-bit codes: into AoS 37.5 us (5.2 TB/s), gathered
 // unit by unit 44; into planes 35 us, one field after another 48 (off the
 // 16-byte grid, gathered, 61).
@@ -2043,13 +2046,13 @@ __device__ __forceinline__ void store_unpack_quads(const Side& s, const Side& d,
   }
 }
 
-// img: the LDS record image of an AoS destination of 4-byte leaves, or null
-// where the plan found no room for it.
+// quads: the plan's choice; img: with it, the LDS record image of an AoS
+// destination of 4-byte leaves.
 template <int CODEC, int U, int DL>
 __device__ __forceinline__ void store_unpack(const Side& s, const Side& d, uint64_t i0, uint32_t nt,
-                                             const uint8_t* lds, uint8_t* img) {
+                                             const uint8_t* lds, bool quads, uint8_t* img) {
   if constexpr (U == 4 && CodecInfo<CODEC>::ES == 4) {
-    if (DL == LY_PLANAR || (DL == LY_AOS && img) || (DL == LY_AOSOA && (d.lanes & 3u) == 0u)) {
+    if (quads) {
       store_unpack_quads<CODEC, DL>(s, d, i0, nt, lds, img);
       return;
     }
