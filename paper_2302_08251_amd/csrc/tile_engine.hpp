@@ -168,8 +168,10 @@ __device__ __forceinline__ void load_tail16(__amdgpu_buffer_rsrc_t rs, uint32_t 
 // and f64 sources of a conversion, which keep the default policy.
 //
 // TAILS: chunks across a blob's end by load_tail16, for the sides that may have
-// many (byte planes); in packs, conversions and unpacks, with one a field at
-// most, its code costs more (64 Mi f64 into 24 bits 164 us, with it 174).
+// many and of any byte length (byte planes); packs, conversions and unpacks, with
+// one a field at most, of whole dwords but for narrow leaves, take the bytes of
+// a partial dword one by one: the other's code cost them more (64 Mi f64 into 24
+// bits 164 us, with it 174).
 template <int LT = -1, int FORM = 0, bool STREAM = true, bool TAILS = true>
 __device__ __forceinline__ void load_tile(const Side& s, uint64_t i0, uint32_t nt, uint8_t* lds) {
   constexpr int L = FORM ? -1 : LT;
@@ -206,7 +208,12 @@ __device__ __forceinline__ void load_tile(const Side& s, uint64_t i0, uint32_t n
         if constexpr (TAILS) {
           load_tail16(rs, chunk * 16u, (uint32_t)left, out);
         } else {
-          for (uint32_t k = 0; k < 16u && k < left; ++k)
+          u32x4 v;
+#pragma unroll
+          for (uint32_t k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, chunk * 16u + 4u * k, 0, 0);
+          *(u32x4*)out = v;
+#pragma unroll 1
+          for (uint32_t k = (uint32_t)left & ~3u; k < (uint32_t)left; ++k)
             out[k] = __builtin_amdgcn_raw_buffer_load_b8(rs, chunk * 16u + k, 0, 0);
         }
       }
