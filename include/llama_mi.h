@@ -346,9 +346,11 @@ llama_status nbody_step(llama_view* particles, uint32_t steps, float dt, float e
  * hipMalloc.  Same kernels, arguments and results as nbody_step (bit for
  * bit), but no library allocation on any call: the per-slice partial
  * accelerations live in a static device array of 16 MiB that each GPU the
- * library runs on holds until the process ends.  That array fits at most
- * 1398101 particles (12 bytes of partial sums per particle and slice of the
- * j range, and as many slices as fit); a larger view returns LLAMA_ERR_NO_MEMORY and
+ * library runs on holds until the process ends.  It holds 12 bytes of
+ * partial sums per particle and slice of the j range; the particle count
+ * decides the number of slices, which never exceeds what the array holds
+ * (one from the size where two no longer fit), so it serves at most 1398101
+ * particles; a larger view returns LLAMA_ERR_NO_MEMORY and
  * nothing is enqueued.  Every call on one GPU shares that GPU's array and
  * writes every element it reads, so nothing needs clearing between calls;
  * calls that overlap in time on one GPU (other streams, other threads) race

@@ -6,7 +6,7 @@
 // 64 bits, bit-packed floats of f16 / bf16 leaves, SPLIT trees with computed
 // parts against a partner of another form; of those, the pairs that the tiled
 // form (k_tree.hip) leaves: sides in different linearisation orders, AoSoA
-// blocks beyond a tile.  One thread takes 32
+// blocks that fit no tile or only a few long ones.  One thread takes 32
 // consecutive records (of the destination's order) and moves them field by
 // field: 32 codes of B bits are exactly B whole stream words, so a bit-packed
 // destination is written without atomics, one word at a time as the codes

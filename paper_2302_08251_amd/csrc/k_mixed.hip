@@ -3,8 +3,9 @@
 // and of SPLIT views (Sec. 3) against a partner that is not divided at the
 // same leaf.  The tile engine moves records as columns of one element size
 // and one mapping; here each thread takes one record and moves its leaves one
-// by one (pairs in one linearisation order with blocks that fit a tile take the
-// tiled form, k_tree.hip), each through the mapping of its own SPLIT part: a leaf is one
+// by one (pairs in one linearisation order with blocks that fit a tile, and not a
+// few long ones only, take the tiled form, k_tree.hip), each through the mapping
+// of its own SPLIT part: a leaf is one
 // naturally aligned load and store where both sides keep it whole and aligned
 // (AoS with C alignment, SoA, AoSoA with aligned blocks), otherwise its bytes
 // move one at a time (packed AoS, Bytesplit byte columns).  The leaf loop is

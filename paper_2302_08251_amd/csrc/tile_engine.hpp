@@ -1002,6 +1002,7 @@ __device__ __forceinline__ void store_window(const Side& d, uint64_t plane, uint
   } else {
     const uint32_t w[4] = {win.x, win.y, win.z, win.w};
     const uint32_t u0 = off < lo ? (lo - off) / U : 0u, u1 = off + 16u > hi ? (hi - off) / U : 16u / U;
+    // a cut window: no mask of 16 bits is the full one
     store_chunk<U>(rs, off, w, ((1u << u1) - 1u) & ~((1u << u0) - 1u), 0x1FFFFu);
   }
 }
