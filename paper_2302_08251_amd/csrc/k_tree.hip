@@ -16,20 +16,22 @@
 // records without padding are put together there; both leave in 16-byte
 // stores after the last leaf.
 //
-// The CU's one scalar unit bounds the small leaves: what a wave decodes per
-// leaf is kept short (the plan holds each leaf's addresses and steps ready, a
-// wave takes a leaf over hundreds of records, K = 8 records a lane share the
-// branches; with the branches taken per record the same copies were up to 2.4
-// times slower).  A store instruction that covers part of a line costs the
-// whole line's write unless the other parts reach L2 at once: hence the images,
-// and the waves working on the leaves of the same records together (padded
-// AoS records: 413 MB written for 120 MB of lines before, 121 MB now).  Such
-// records' lines leave with holes, which the memory fills by reading: they
-// bound the padded destinations (stored by full dwords and bytes from an image,
-// with half the requests, they took the same time).
+// Half of a wave's cycles wait for memory: a tile's loads, leaves and stores
+// follow each other.  Scalar issue takes 21-44 % of the time and vector issue
+// 11-48 %, so what a wave decodes per leaf is kept short (the plan holds each
+// leaf's addresses and steps ready, a wave takes a leaf over hundreds of records,
+// K = 8 records a lane share the branches; with the branches taken per record the
+// same copies were up to 2.4 times slower).  A store instruction that covers part
+// of a line costs the whole line's write unless the other parts reach L2 at once:
+// hence the images, and the waves working on the leaves of the same records
+// together (padded AoS records: 130 MB written for 120 MB of lines, 413 MB with
+// the leaves one after another).  Such records' stores leave holes in every line:
+// waves wait 57 % of their cycles to issue, against 15-30 % elsewhere, and the
+// copy moves 3.6 TB/s (stored by full dwords and bytes from an image, with half
+// the requests, it took the same time).
 //
 // 5 Mi records {u8, f64, i16, f32} (150 MB moved a copy) in 27-37 us, padded
-// AoS destinations in 64 us; one thread per record and leaf took 77-114 us.
+// AoS destinations in 57-64 us; one thread per record and leaf took 77-114 us.
 // 3 Mi records of 3 integers between i32, i16 and 12-bit codes in 20-25 us, one
 // thread per 32 records took 130-237 us.  (K = 4: 8 Mi records of 7 leaves into
 // AoS 87 us, K = 8 70; the other copies within 5 %.)

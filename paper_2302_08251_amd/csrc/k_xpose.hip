@@ -10,13 +10,16 @@
 // access is one contiguous run.  The LDS image is [unit][q][p] with padded
 // rows, which keeps the column writes nearly free of bank conflicts.
 //
-// Bound by the lines at the ends of the runs, which lie off the line grid: two
-// tiles read or write each of them.  So neighbouring tiles run on the same XCD
-// (its L2 then merges the parts; without that order 20-30 % slower), and the
-// runs are 256 bytes or more.  A lane keeps its place in the run and steps
-// through the rows with one addition, eight accesses in flight; with 64-bit
-// index arithmetic per unit and 128-byte runs 15.6 Mi records of 3 x f32, AoS
-// to column-major SoA, took 237 us against 92 (4.1 TB/s).
+// No one resource is full: a tile's loads, its barrier and its stores follow
+// each other, so half of a wave's cycles wait for memory, while vector issue
+// takes half of the time and scalar issue a third (15.6 Mi records of 3 x f32,
+// AoS to column-major SoA: 92 us, 4.1 TB/s; 1.01 times the needed bytes read,
+// 1.05 written).  The lines at the runs' ends lie off the line grid and belong to
+// two tiles; neighbouring tiles run on the same XCD, whose L2 merges all but 2 %
+// of them (without that order 20-30 % slower).  Runs are 256 bytes on axes that
+// hold them.  A lane keeps its place in the run and steps through the rows with
+// one addition, eight accesses in flight; with 64-bit index arithmetic per unit
+// and 128-byte runs the same copy took 237 us.
 #include "kernels.hpp"
 
 namespace lm {
